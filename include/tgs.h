@@ -348,8 +348,11 @@ tgs_status tgs_scene_set_sort_path(tgs_scene *scene, int32_t mode);
  * scheduling).  The few longest lists set the blend's tail; a quadrant
  * block re-reads the whole list, so shorter ones are cheaper unsplit.
  * log2_min in [0, 31], or -1 for no split; max_tiles in [0,
- * TGS_BLEND_SPLIT_MAX].  Defaults: TGS_BLEND_SPLIT_DEFAULT,
- * TGS_BLEND_SPLIT_MAX.  INVALID_ARG for a NULL scene or other values. */
+ * TGS_BLEND_SPLIT_MAX].  A scene on which it was never called splits at most
+ * TGS_BLEND_SPLIT_MAX tiles, from a threshold that follows each frame: its
+ * keys / 1024 rounded up to a power of two, at least 32 and at most
+ * 2^TGS_BLEND_SPLIT_DEFAULT (frames with few keys leave the chip idle behind
+ * their longest lists).  INVALID_ARG for a NULL scene or other values. */
 enum { TGS_BLEND_SPLIT_DEFAULT = 12, TGS_BLEND_SPLIT_MAX = 1024 };
 tgs_status tgs_scene_set_blend_split(tgs_scene *scene, int32_t log2_min, int32_t max_tiles);
 

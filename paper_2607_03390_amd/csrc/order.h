@@ -20,6 +20,24 @@ __device__ inline uint32_t length_bucket(const uint2 *ranges, int t) {
     return len ? 32u - (uint32_t)__clz(len) : 0u;
 }
 
+// Length bucket from which a frame of n_keys keys splits its tiles, at most
+// most: lists of at least the keys that 1024 evenly loaded blocks would each
+// hold, rounded up to a power of two, but no shorter than 32.  A list longer
+// than that is still walked when the rest of the chip has run dry (about
+// 2048 tile blocks are resident at once), so its tile sets the launch's tail
+// and four quadrant blocks shorten it; shorter ones are only staged four
+// times for nothing.  Measured at thresholds of 2^5 .. 2^13 (blend launch,
+// microseconds): 34k keys on 256 tiles 17.4 up to 2^8, 24.4 from 2^9;
+// 107k keys on 920 tiles with every output 107 up to 2^9, 110 at 2^10, 251
+// at 2^12; 731k keys on 3600 tiles 66 at 2^5, 60.9 at 2^10, 104 at 2^12;
+// 562k - 1.1M keys on the selected tiles of a room 72 up to 2^8, 58.8 from
+// 2^10; 5.0M keys on 8160 tiles 112 at 2^5, 105 from 2^9.
+__device__ inline int split_bucket_for(uint32_t n_keys, int most) {
+    const uint32_t mean = n_keys >> 10;
+    const int lg = mean > 32u ? 32 - __clz(mean - 1u) : 5;
+    return lg + 1 < most ? lg + 1 : most;
+}
+
 constexpr int kOrderBuckets = 33;
 // LDS words of order_tiles_block<NT, ...>: bucket counters per wave (at
 // most).
@@ -84,7 +102,8 @@ __device__ inline void order_bucket_starts(const OrderK &o, uint32_t *s_cnt) {
     // the tiles the blend splits, a prefix of the order: those of the
     // buckets from the lowest one >= split_bucket that leaves at most
     // max_split tiles in it and above (whole buckets)
-    const int sb = o.split_bucket;
+    const int sb = o.n_keys && o.split_bucket >= 1 ? split_bucket_for(*o.n_keys, o.split_bucket)
+                                                   : o.split_bucket;
     const uint64_t fit = __ballot(sb >= 1 && b >= sb && inc <= (uint32_t)o.max_split);
     const uint32_t ns = __shfl(inc, fit ? 63 - __clzll((long long)fit) : 0);
     if (o.n_split && tid == 0) *o.n_split = fit ? ns : 0u;

@@ -352,7 +352,9 @@ struct tgs_scene {
     // always the global depth sort, 2 = always the per-tile sort
     int sort_path = TGS_SORT_AUTO;
     // list length bucket from which the blend splits tiles into quadrants
-    // (0: never), and the most tiles split
+    // (0: never; split_auto: an upper bound, each frame takes its own from
+    // its keys), and the most tiles split
+    bool split_auto = true;
     int split_bucket = tgs::kSplitBucket;
     int split_max = tgs::kMaxSplit;
     DevBuf data;
@@ -559,6 +561,7 @@ tgs_status step_keys(const tgs_scene *sc, Workspace &ws, int TX, int TY, const u
     order.n_split = &cnt->n_split;
     order.split_bucket = sc->split_bucket;
     order.max_split = sc->split_max;
+    order.n_keys = sc->split_auto ? &cnt->n_sorted : nullptr;
     if (ws.frame_seg) {
         // each tile's list, emitted in index order, by (depth bits, index)
         ProfScope ps(TGS_PROF_SORT, st);
@@ -659,6 +662,7 @@ tgs_status tgs_scene_set_blend_split(tgs_scene *scene, int32_t log2_min, int32_t
     if (log2_min < -1 || log2_min > 31) return fail(TGS_ERR_INVALID_ARG, "log2_min must be in [-1, 31]");
     if (max_tiles < 0 || max_tiles > kMaxSplit)
         return fail(TGS_ERR_INVALID_ARG, "max_tiles must be in [0, " + std::to_string(kMaxSplit) + "]");
+    scene->split_auto = false;
     scene->split_bucket = log2_min + 1;
     scene->split_max = max_tiles;
     return TGS_OK;

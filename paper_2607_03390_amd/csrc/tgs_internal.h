@@ -202,9 +202,12 @@ struct OrderK {
     // order: those whose list length bucket is at least split_bucket, or, if
     // more than max_split (<= kMaxSplit) are, at least the lowest higher
     // bucket that leaves at most max_split (0: no split)
+    // n_keys (optional): the frame's key count; split_bucket is then an upper
+    // bound and the frame's own is taken from its mean load (split_bucket_for)
     uint32_t *n_split;
     int split_bucket;
     int max_split;
+    const uint32_t *n_keys;
 };
 void launch_order_tiles(const OrderK &o, hipStream_t st);
 

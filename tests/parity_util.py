@@ -321,7 +321,8 @@ class Uploaded:
         self.h = tgs.tgs_scene_upload(self.scene)
         tgs.tgs_scene_set_tile_bound(self.h, self.bound)
         tgs.tgs_scene_set_sort_path(self.h, self.sort)
-        tgs.tgs_scene_set_blend_split(self.h, *self.split)
+        if self.split is not None:   # None: the threshold follows each frame
+            tgs.tgs_scene_set_blend_split(self.h, *self.split)
         return self.h
 
     def __exit__(self, *a):

@@ -179,6 +179,34 @@ def test_split_blend_full_parity(split_all, n, seed, deg, W, H):
     _full_parity(sc, cams, label=f"split {W}x{H}")
 
 
+@pytest.fixture
+def split_auto():
+    """The split threshold follows each frame's keys (the default of a scene)."""
+    SETTINGS["split"] = None
+    yield
+    SETTINGS["split"] = (tgs.BLEND_SPLIT_DEFAULT, tgs.BLEND_SPLIT_MAX)
+
+
+# fewer than 32 keys per 1024 (threshold 32), a threshold between the two
+# bounds, and one past the most tiles that are split
+@pytest.mark.parametrize("n,log_scale,W,H", [(700, -3.0, 200, 136), (24_000, -2.6, 48, 40),
+                                             (20_000, -4.0, 641, 359)])
+def test_split_auto_full_parity(split_auto, n, log_scale, W, H):
+    """Tiles split from the frame's own threshold: images, moments and the
+    Gaussian buffer against the oracle."""
+    sc = synth.scene_uniform_cube(n, 11, degree=1, log_scale_mean=log_scale)
+    cam = synth.make_camera(synth.look_at((0.3, -4.0, 0.5), (0, 0, 0)), W, H)
+    _full_parity(sc, [cam], label=f"split auto {W}x{H}")
+
+
+def test_split_auto_temporal_parity(split_auto):
+    """TemporalGS frames take their threshold from the keys of the selected
+    tiles."""
+    sc = synth.scene_room(60_000, 2)
+    cams = synth.handheld_path(7, (0.0, -5.0, 0.3), (0.0, 0.0, 0.0), 0.3, 0.01, 401, 233)
+    assert _temporal_parity(sc, cams, 401, 233, "split auto room60k")["tgs"] >= 3
+
+
 def test_split_blend_long_lists(split_all):
     """Quadrant blocks on lists of several thousand entries (many batches,
     pixels stopping inside a group of four entries)."""

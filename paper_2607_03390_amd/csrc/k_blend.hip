@@ -45,9 +45,8 @@ __device__ inline bool wave_all(bool p) { return __builtin_amdgcn_ballot_w64(!p)
 // Broadcast of lane K of each group of four lanes (DPP quad_perm).
 template <int K>
 __device__ inline float quad_bcast(float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v),
-                                                              K | (K << 2) | (K << 4) | (K << 6),
-                                                              0xf, 0xf, false));
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
+        0, __builtin_bit_cast(int, v), K | (K << 2) | (K << 4) | (K << 6), 0xf, 0xf, true));
 }
 template <int K>
 __device__ inline uint32_t quad_bcast_u(uint32_t v) {
@@ -88,6 +87,7 @@ __device__ inline float quad_sum(float v) {
 // alpha >= 1/255 ellipse, conservatively enlarged, meets the sub-block, in
 // staging (= depth) order: a footprint a few pixels wide meets a 4x4 block
 // about 60 % as often as the 8x8 quadrant.
+template <bool COUNT>
 struct BlendLds {
     float4 g0[256];
     float4 g1[256];
@@ -95,7 +95,270 @@ struct BlendLds {
     int idx[256];
     __align__(16) uint8_t list[16][256];
     __align__(16) uint16_t mask[256];   // sub-blocks each staged Gaussian meets
+    uint32_t cnt[2][4];                 // quadrant: kept entries per wave
+    uint32_t pos[COUNT ? 256 : 1];      // quadrant: list position of each slot
 };
+
+// One pixel's running sums.
+struct PixelSums {
+    float T, cr, cg, cb;
+    float sw, s1, s2, d0;
+    bool pivot;
+    uint64_t done;       // stopped lanes of the wave (on scalar registers: tested
+                         // and updated without vector instructions)
+    uint32_t stop_pos;   // list position of the stopping Gaussian (+1 below)
+    uint32_t n_hit;      // pairs with alpha >= 1/255 before the pixel stopped
+};
+
+// The wave's walk over its sub-block list, four lanes per pixel on four
+// consecutive entries, two such groups per iteration (n_run entries, the
+// list padded with sentinels to a multiple of eight).  Few waves share a SIMD
+// when a long tile sets the launch's tail, so an iteration's latency counts:
+// both groups' records are loaded and their alphas formed before the first
+// product of the transmittance chain, every choice is a select on a wave
+// mask, and the one exception (a pixel stops) is a wave-uniform branch.
+// (With the choices left to the compiler it branched ten times per group.)
+template <bool CAPTURE, bool CONTRIB, bool COUNT>
+__device__ __attribute__((always_inline)) inline void quad_walk(const BlendArgs &a, BlendLds<COUNT> &s,
+                                                                PixelSums &p, float fpx, float fpy,
+                                                                int my_list, uint32_t n_run) {
+    constexpr int kU = 2;
+    // lanes of entries 1..3, 2..3 and 3 of every group
+    constexpr uint64_t kFrom1 = 0xeeeeeeeeeeeeeeeeull, kFrom2 = 0xccccccccccccccccull,
+                       kFrom3 = 0x8888888888888888ull;
+    const int lane = threadIdx.x & 63, k = lane & 3;
+    const uint8_t *list = &s.list[my_list][k];
+    const char *sg0 = reinterpret_cast<const char *>(s.g0);
+    for (uint32_t e = 0; e < n_run; e += 4 * kU) {
+        uint32_t jo[kU];   // byte offsets into the staged arrays
+#pragma unroll
+        for (int u = 0; u < kU; ++u) jo[u] = (uint32_t)list[e + 4 * u] << 4;
+        float p2[kU], alpha[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const float4 g0 = *reinterpret_cast<const float4 *>(sg0 + jo[u]);
+            const float2 g1 = *reinterpret_cast<const float2 *>(reinterpret_cast<const char *>(s.g1) + jo[u]);
+            const float dx = g0.x - fpx, dy = g0.y - fpy;
+            p2[u] = __builtin_fmaf(dx, __builtin_fmaf(g0.z, dx, g0.w * dy), g1.x * dy * dy);
+            alpha[u] = fminf(kAlphaMax, g1.y * __builtin_amdgcn_exp2f(p2[u]));
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            // a running pixel's entry with power <= 0 and alpha >= 1/255
+            const uint64_t hitm = __builtin_amdgcn_ballot_w64(!(p2[u] > 0.0f)) &
+                                  __builtin_amdgcn_ballot_w64(alpha[u] >= kAlphaMin) & ~p.done;
+            // transmittance through the four entries in list order, one
+            // product at a time (the fp32 products of a sequential walk;
+            // an entry that is no hit multiplies by exactly 1)
+            const float f = __builtin_amdgcn_inverse_ballot_w64(hitm) ? 1.0f - alpha[u] : 1.0f;
+            const float t1 = p.T * quad_bcast<0>(f);
+            const float t2 = t1 * quad_bcast<1>(f);
+            const float t3 = t2 * quad_bcast<2>(f);
+            const float t4 = t3 * quad_bcast<3>(f);
+            float Tin = __builtin_amdgcn_inverse_ballot_w64(kFrom1) ? t1 : p.T;
+            Tin = __builtin_amdgcn_inverse_ballot_w64(kFrom2) ? t2 : Tin;
+            Tin = __builtin_amdgcn_inverse_ballot_w64(kFrom3) ? t3 : Tin;
+            // the products never grow, so an entry whose own product (bit
+            // for bit the chain's) stays above 1e-4 is composited: the pixel
+            // stopped neither there nor before.  (The entry whose product
+            // falls below, a hit, is not composited.)
+            const uint64_t keepm = __builtin_amdgcn_ballot_w64(Tin * f >= kTMin);
+            const bool inc = __builtin_amdgcn_inverse_ballot_w64(hitm & keepm);
+            const float w = inc ? alpha[u] * Tin : 0.0f;
+            const float4 c = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(s.col) + jo[u]);
+            p.cr = __builtin_fmaf(w, c.x, p.cr);
+            p.cg = __builtin_fmaf(w, c.y, p.cg);
+            p.cb = __builtin_fmaf(w, c.z, p.cb);
+            const uint64_t stopm = __builtin_amdgcn_ballot_w64(!(t4 >= kTMin));
+            if (COUNT) {
+                // hits up to and including the stopping entry: composited, or
+                // the first one of its group that is not
+                const uint64_t out = hitm & ~keepm;
+                const uint64_t first = out & ~((out & ~kFrom3) << 1 | (out & ~kFrom2) << 2 |
+                                               (out & ~kFrom1) << 3);
+                p.n_hit += __builtin_amdgcn_inverse_ballot_w64((hitm & keepm) | first) ? 1u : 0u;
+            }
+            float T = t4;
+            if (stopm) {
+                // pixels that stop in this group keep the product before it
+                const float ts = t3 >= kTMin ? t3 : t2 >= kTMin ? t2 : t1 >= kTMin ? t1 : p.T;
+                T = __builtin_amdgcn_inverse_ballot_w64(stopm) ? ts : T;
+                if (COUNT) {
+                    const uint32_t j = jo[u] >> 4;
+                    const uint32_t jk = t3 >= kTMin ? quad_bcast_u<3>(j) : t2 >= kTMin ? quad_bcast_u<2>(j)
+                                      : t1 >= kTMin ? quad_bcast_u<1>(j) : quad_bcast_u<0>(j);
+                    if (__builtin_amdgcn_inverse_ballot_w64(stopm)) p.stop_pos = s.pos[jk];
+                }
+            }
+            p.T = T;
+            if (CAPTURE) {
+                const float dep = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(s.g1) + jo[u] + 8);
+                // the pivot: depth of the pixel's first composited entry
+                if (__builtin_amdgcn_ballot_w64(inc && !p.pivot)) {
+                    const int km0 = inc ? k : 4;
+                    int km = min(km0, (int)__builtin_amdgcn_mov_dpp(km0, 0xb1, 0xf, 0xf, false));
+                    km = min(km, (int)__builtin_amdgcn_mov_dpp(km, 0x4e, 0xf, 0xf, false));
+                    const float dk = km == 0 ? quad_bcast<0>(dep) : km == 1 ? quad_bcast<1>(dep)
+                                   : km == 2 ? quad_bcast<2>(dep) : quad_bcast<3>(dep);
+                    p.d0 = (!p.pivot && km < 4) ? dk : p.d0;
+                    p.pivot = p.pivot || km < 4;
+                }
+                const float dd = dep - p.d0;
+                p.sw += w;
+                p.s1 = __builtin_fmaf(w, dd, p.s1);
+                p.s2 = __builtin_fmaf(w * dd, dd, p.s2);
+                if (inc) *reinterpret_cast<float *>(reinterpret_cast<char *>(s.g1) + jo[u] + 12) = 1.0f;
+                if (CONTRIB) {
+                    // max weight of this lane's entry over the wave's 16 pixels
+                    float mw = w;
+#pragma unroll
+                    for (int o = 4; o <= 32; o <<= 1) mw = fmaxf(mw, __shfl_xor(mw, o));
+                    if (lane < 4 && mw > 0.0f)
+                        atomicMax(reinterpret_cast<unsigned int *>(a.contrib + s.idx[jo[u] >> 4]),
+                                  __float_as_uint(mw));
+                }
+            }
+            p.done |= stopm;
+        }
+        if (p.done == ~0ull) break;
+    }
+}
+
+// The batches of a quadrant block.  A list is long here (its tile sets the
+// launch's tail) and few blocks are left to hide its latency, so the list
+// is read ahead and thinned out before it is staged: each step tests 255
+// entries against the quadrant's four sub-blocks and appends the ones that
+// meet any (in list order: wave ballots, the counts of the four waves through
+// LDS, one barrier) to the staged slots, which are walked once all are taken
+// (a step's entries past the last slot go to the next filling).  A quadrant
+// meets about 40 % of its tile's small Gaussians, so the walk, its lists and
+// its barriers run that much more seldom.  Indices are loaded two steps
+// ahead and one word of every record one step ahead, so that a step's gather
+// finds its lines in the cache instead of waiting for memory.  With the walk
+// above: a street scene's lists of 16k entries (9.9M keys on 8160 tiles)
+// 531 -> 345 us for the full-render blend, 624 -> 460 us with the Eq. 1/2
+// capture, 107k keys on 920 tiles with every output 107 -> 84 us, 34k keys on
+// 256 tiles 17.4 -> 13.5 us.
+template <bool CAPTURE, bool CONTRIB, bool COUNT>
+__device__ __attribute__((always_inline)) inline void quad_batches(const BlendArgs &a, BlendLds<COUNT> &s,
+                                                                   PixelSums &p, uint2 range,
+                                                                   float qx0, float qy0, int my_list,
+                                                                   float fpx, float fpy) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (tid == kBatch) {   // the sentinel
+        s.g0[tid] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        s.g1[tid] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        s.col[tid] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        s.idx[tid] = 0;
+        if (COUNT) s.pos[tid] = 0u;
+    }
+    // walks the fill staged slots; true once every pixel of the block has stopped
+    auto flush = [&](uint32_t fill) -> bool {
+        __syncthreads();
+        uint8_t *list = &s.list[my_list][0];
+        reinterpret_cast<uint32_t *>(list)[lane] = 0xffffffffu;
+        // lane l lists slots 4l .. 4l + 3 of the wave's sub-block
+        const uint2 m4 = reinterpret_cast<const uint2 *>(s.mask)[lane];
+        uint32_t own = __builtin_amdgcn_ubfe(m4.x, wave, 1) | __builtin_amdgcn_ubfe(m4.x, 16 + wave, 1) << 1 |
+                       __builtin_amdgcn_ubfe(m4.y, wave, 1) << 2 |
+                       __builtin_amdgcn_ubfe(m4.y, 16 + wave, 1) << 3;
+        const int left = (int)fill - 4 * lane;
+        own &= left >= 4 ? 15u : left > 0 ? (1u << left) - 1u : 0u;
+        const uint32_t n_own = (uint32_t)__popc(own);
+        const uint32_t incl = wave_incl_sum_bytes(n_own);
+        uint32_t o = incl - n_own;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if ((own >> j) & 1u) list[o] = (uint8_t)(4 * lane + j);
+            o += (own >> j) & 1u;
+        }
+        const uint32_t n_list = __builtin_amdgcn_readlane(incl, 63);
+        quad_walk<CAPTURE, CONTRIB, COUNT>(a, s, p, fpx, fpy, my_list, p.done == ~0ull ? 0u : n_list);
+        const bool all = __syncthreads_and(p.done == ~0ull) != 0;
+        if (CAPTURE) {
+            if (a.g_flag && tid < (int)fill && s.g1[tid].w != 0.0f) a.g_flag[s.idx[tid]] = 1u;
+            __syncthreads();
+        }
+        return all;
+    };
+    auto entry = [&](uint32_t b) -> int {
+        return tid < kBatch && b + tid < range.y ? (int)a.vals[b + tid] : 0;
+    };
+    int i0 = entry(range.x), i1 = entry(range.x + kBatch);
+    uint32_t fill = 0u;
+    int step = 0;
+    for (uint32_t b = range.x;; b += kBatch, step ^= 1) {
+        const bool last = b >= range.y;   // block-uniform: only the walk is left
+        if (last && fill == 0u) return;
+        const float4 *r = a.g + 4 * (size_t)i0;
+        const float4 r0 = r[0], r1 = r[1], r2 = r[2], r3 = r[3];
+        const float warm = a.g[4 * (size_t)i1].x;
+        const int i2 = last ? 0 : entry(b + 2 * kBatch);
+        uint32_t bits = 0u;
+        const float hx = r2.w, hy = r1.w;
+        if (tid < kBatch && b + tid < range.y && hx >= 0.0f) {
+            // the tests of a whole tile (below), on the quadrant's sub-blocks:
+            // bit g: column g & 1, row g >> 1
+            const float ca = r0.z, cbq = r0.w, cc = r1.x;
+            const float m = __builtin_amdgcn_sqrtf(2.25f * (ca + cc + 2.0f * fabsf(cbq)));
+            const float rr = (__builtin_amdgcn_sqrtf(r3.w) + m) * 1.002f + 0.01f;
+            const float R = rr * rr;
+            float ax[2], bx[2], dyr[2], cy2[2];
+            uint32_t box = 0u, rows = 0u;
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const float x0 = qx0 + 4.0f * c, y0 = qy0 + 4.0f * c;
+                box |= (r0.x + hx >= x0 && r0.x - hx <= x0 + 3.0f) ? 5u << c : 0u;
+                rows |= (r0.y + hy >= y0 && r0.y - hy <= y0 + 3.0f) ? 3u << (2 * c) : 0u;
+                const float dx = x0 + 1.5f - r0.x, dy = y0 + 1.5f - r0.y;
+                ax[c] = ca * dx * dx;
+                bx[c] = 2.0f * cbq * dx;
+                dyr[c] = dy;
+                cy2[c] = cc * dy * dy;
+            }
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const float qf = __builtin_fmaf(bx[g & 1], dyr[g >> 1], ax[g & 1] + cy2[g >> 1]);
+                bits |= !(qf > R) ? (1u << g) : 0u;
+            }
+            bits &= box & rows;
+        }
+        const uint64_t keep = __ballot(bits != 0u);
+        if (lane == 0) s.cnt[step][wave] = (uint32_t)__popcll(keep);
+        __syncthreads();
+        uint32_t total = 0u, off = (uint32_t)__popcll(keep & ((1ull << lane) - 1ull));
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const uint32_t c = s.cnt[step][w];
+            if (w < wave) off += c;
+            total += c;
+        }
+        // slot of the kept entry: past the last one, that of the next filling
+        uint32_t o = fill + off;
+        auto stage = [&]() {
+            s.g0[o] = make_float4(r0.x, r0.y, r3.x, r3.y);
+            s.g1[o] = make_float4(r3.z, r1.y, r1.z, 0.0f);
+            s.col[o] = r2;
+            s.idx[o] = i0;
+            s.mask[o] = (uint16_t)bits;
+            if (COUNT) s.pos[o] = b + tid;
+        };
+        fill += __builtin_amdgcn_readfirstlane(total);
+        if (bits && o < (uint32_t)kBatch) stage();
+        if (last || fill >= (uint32_t)kBatch) {   // block-uniform
+            if (flush(min(fill, (uint32_t)kBatch)) || last) return;
+            fill -= kBatch;
+            if (bits && o >= (uint32_t)kBatch) {
+                o -= kBatch;
+                stage();
+            }
+        }
+        // the word of the next step's record has arrived: its line is in the cache
+        __asm__ volatile("" ::"v"(warm));
+        i0 = i1;
+        i1 = i2;
+    }
+}
 
 // One 16x16 tile, or (QUAD) one 8x8 quadrant q of it.
 //  - tile: each wave covers an 8x8 quadrant as four 16-lane groups, one per
@@ -107,7 +370,7 @@ struct BlendLds {
 //    in list order through the quad's transmittance products.  The four
 //    blocks of a tile each stage the whole list.
 template <bool CAPTURE, bool CONTRIB, bool COUNT, bool QUAD>
-__device__ __attribute__((always_inline)) inline void blend_block(const BlendArgs &a, BlendLds &s,
+__device__ __attribute__((always_inline)) inline void blend_block(const BlendArgs &a, BlendLds<COUNT> &s,
                                                                   int tile, int q) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int tx = tile % a.TX, ty = tile / a.TX;
@@ -148,6 +411,22 @@ __device__ __attribute__((always_inline)) inline void blend_block(const BlendArg
     uint32_t stop_pos = range.y;   // list position of the stopping Gaussian (+1 below)
     uint32_t n_hit = 0;            // pairs with alpha >= 1/255 before the pixel stopped
 
+    if (QUAD) {
+        const float qx0 = tile_x0 + (float)(8 * (q & 1)), qy0 = tile_y0 + (float)(8 * (q >> 1));
+        PixelSums p{T, cr, cg, cb, sw, s1, s2, d0, pivot, done, stop_pos, n_hit};
+        if (qx0 < (float)a.W && qy0 < (float)a.H)   // block-uniform: the quadrant has pixels
+            quad_batches<CAPTURE, CONTRIB, COUNT>(a, s, p, range, qx0, qy0, my_list, fpx, fpy);
+        T = p.T;
+        cr = p.cr;
+        cg = p.cg;
+        cb = p.cb;
+        sw = p.sw;
+        s1 = p.s1;
+        s2 = p.s2;
+        d0 = p.d0;
+        stop_pos = p.stop_pos;
+        n_hit = p.n_hit;
+    }
     // Batches of 255 Gaussians in slots 0..254; slot 255 holds a sentinel
     // (opacity 0, conic 0: alpha 0 at every pixel) that pads every list, so
     // entries past a list's end need no test of their own.
@@ -155,8 +434,8 @@ __device__ __attribute__((always_inline)) inline void blend_block(const BlendArg
     // batch is blended: a batch then waits for one dependent global load
     // (its records) instead of two, which sets the pace of the tiles with
     // thousands of batches
-    int nidx = (tid < kBatch && range.x + tid < range.y) ? (int)a.vals[range.x + tid] : 0;
-    for (uint32_t b = range.x; b < range.y; b += kBatch) {
+    int nidx = (!QUAD && tid < kBatch && range.x + tid < range.y) ? (int)a.vals[range.x + tid] : 0;
+    for (uint32_t b = range.x; !QUAD && b < range.y; b += kBatch) {
         if (__syncthreads_and(done == ~0ull)) break;
         reinterpret_cast<uint4 *>(&s.list[0][0])[tid] =
             make_uint4(0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu);
@@ -223,20 +502,17 @@ __device__ __attribute__((always_inline)) inline void blend_block(const BlendArg
                     lists |= !(qf > R) ? (1u << L) : 0u;
                 }
                 lists &= box;
-                // a quadrant block lists its own four sub-blocks only
-                if (QUAD) lists &= 0xfu << (4 * q);
             }
         }
         // Order-preserving compaction: every staged Gaussian's sub-block
-        // bits go to LDS, then each wave builds the lists it walks (tile:
-        // its four sub-blocks; quadrant: its one) from all the staged
-        // Gaussians.  Lane l takes slots 4l .. 4l + 3; its entries' offsets
+        // bits go to LDS, then each wave builds the four lists it walks from
+        // all the staged Gaussians.  Lane l takes slots 4l .. 4l + 3; its entries' offsets
         // are one wave-wide prefix sum of its per-list counts, four lists
         // packed one byte each (a list holds at most 255 entries).
         s.mask[tid] = (uint16_t)lists;
         __syncthreads();
-        constexpr int kNL = QUAD ? 1 : 4;
-        const int L0 = QUAD ? my_list : 4 * wave;
+        constexpr int kNL = 4;
+        const int L0 = 4 * wave;
         const uint2 m4 = reinterpret_cast<const uint2 *>(s.mask)[lane];
         uint32_t own[kNL], packed = 0;
 #pragma unroll
@@ -263,160 +539,83 @@ __device__ __attribute__((always_inline)) inline void blend_block(const BlendArg
             n_long = max(n_long, (tot >> (8 * gl)) & 255u);
         }
         // the wave's trip count, the same for every lane (on scalar
-        // registers): its longest list (tile; shorter lists are padded), or
-        // its list's length rounded up to whole groups of four (quadrant).
+        // registers): its longest list (shorter lists are padded).
         // The wave reads only the lists it wrote: no barrier before the walk.
-        if (QUAD) n_long = (n_long + 3u) & ~3u;
         {
             const uint32_t kn = b + kBatch + tid;
             nidx = (tid < kBatch && kn < range.y) ? (int)a.vals[kn] : 0;
         }
         // a wave whose pixels have all stopped skips the batch
         const uint32_t n_run = done == ~0ull ? 0u : n_long;
-        if (QUAD) {
-            for (uint32_t e = 0; e < n_run; e += 4) {
-                // the group's four slots in one aligned 32-bit LDS load
-                const uint32_t j = (*reinterpret_cast<const uint32_t *>(&s.list[my_list][e]) >> (8 * k)) & 255u;
-                const uint32_t jo = j << 4;   // byte offset into the staged arrays
-                const float4 g0 = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(s.g0) + jo);
-                const float4 g1 = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(s.g1) + jo);
-                const float dx = g0.x - fpx, dy = g0.y - fpy;
-                const float p2 = __builtin_fmaf(dx, __builtin_fmaf(g0.z, dx, g0.w * dy), g1.x * dy * dy);
-                const float alpha = fminf(kAlphaMax, g1.y * __builtin_amdgcn_exp2f(p2));
-                // a running pixel's entry with power <= 0 and alpha >= 1/255
-                const uint64_t hitm = __builtin_amdgcn_ballot_w64(!(p2 > 0.0f)) &
-                                      __builtin_amdgcn_ballot_w64(alpha >= kAlphaMin) & ~done;
-                const bool hit = __builtin_amdgcn_inverse_ballot_w64(hitm);
-                // transmittance through the four entries in list order, one
-                // product at a time (the fp32 products of a sequential walk;
-                // an entry that is no hit multiplies by exactly 1)
-                const float f = hit ? 1.0f - alpha : 1.0f;
-                const float t1 = T * quad_bcast<0>(f);
-                const float t2 = t1 * quad_bcast<1>(f);
-                const float t3 = t2 * quad_bcast<2>(f);
-                const float t4 = t3 * quad_bcast<3>(f);
-                // the pixel stops at the first entry whose product falls
-                // below 1e-4 (a hit; that entry is not composited)
-                const int ks = !(t1 >= kTMin) ? 0 : !(t2 >= kTMin) ? 1 : !(t3 >= kTMin) ? 2
-                             : !(t4 >= kTMin) ? 3 : 4;
-                const float Tin = k == 0 ? T : k == 1 ? t1 : k == 2 ? t2 : t3;
-                const bool inc = hit && k < ks;
-                const float w = inc ? alpha * Tin : 0.0f;
-                const float4 c = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(s.col) + jo);
-                cr = __builtin_fmaf(w, c.x, cr);
-                cg = __builtin_fmaf(w, c.y, cg);
-                cb = __builtin_fmaf(w, c.z, cb);
-                const bool stopping = ks < 4;
-                T = ks == 0 ? T : ks == 1 ? t1 : ks == 2 ? t2 : ks == 3 ? t3 : t4;
-                if (COUNT) {
-                    n_hit += (hit && k <= ks) ? 1u : 0u;
-                    if (stopping) {
-                        const uint32_t jk = ks == 0 ? quad_bcast_u<0>(j) : ks == 1 ? quad_bcast_u<1>(j)
-                                          : ks == 2 ? quad_bcast_u<2>(j) : quad_bcast_u<3>(j);
-                        stop_pos = b + jk;
-                    }
-                }
-                if (CAPTURE) {
-                    const float dep = g1.z;
-                    // the pivot: depth of the pixel's first composited entry
-                    if (__builtin_amdgcn_ballot_w64(inc && !pivot)) {
-                        const int km0 = inc ? k : 4;
-                        int km = min(km0, (int)__builtin_amdgcn_mov_dpp(km0, 0xb1, 0xf, 0xf, false));
-                        km = min(km, (int)__builtin_amdgcn_mov_dpp(km, 0x4e, 0xf, 0xf, false));
-                        const float dk = km == 0 ? quad_bcast<0>(dep) : km == 1 ? quad_bcast<1>(dep)
-                                       : km == 2 ? quad_bcast<2>(dep) : quad_bcast<3>(dep);
-                        d0 = (!pivot && km < 4) ? dk : d0;
-                        pivot = pivot || km < 4;
-                    }
-                    const float dd = dep - d0;
-                    sw += w;
-                    s1 = __builtin_fmaf(w, dd, s1);
-                    s2 = __builtin_fmaf(w * dd, dd, s2);
-                    if (inc) *reinterpret_cast<float *>(reinterpret_cast<char *>(s.g1) + jo + 12) = 1.0f;
-                    if (CONTRIB) {
-                        // max weight of this lane's entry over the wave's 16 pixels
-                        float mw = w;
+        // list slots are read four at a time (one aligned 32-bit LDS load
+        // per four entries, each slot's byte offset taken with constant
+        // shifts): three entries in four wait for one LDS round trip (the
+        // staged record) instead of two.  The walk runs to the wave's
+        // longest list rounded up to four: the slots past every list's
+        // end hold the sentinel (alpha 0)
+        bool stopped = false;
+        for (uint32_t e = 0; e < n_run && !stopped; e += 4) {
+          const uint32_t quad = *reinterpret_cast<const uint32_t *>(&s.list[my_list][e]);
 #pragma unroll
-                        for (int o = 4; o <= 32; o <<= 1) mw = fmaxf(mw, __shfl_xor(mw, o));
-                        if (lane < 4 && mw > 0.0f)
-                            atomicMax(reinterpret_cast<unsigned int *>(a.contrib + s.idx[j]),
-                                      __float_as_uint(mw));
-                    }
-                }
-                done |= __builtin_amdgcn_ballot_w64(stopping);
-                if (done == ~0ull) break;
+          for (int u = 0; u < 4; ++u) {
+            // byte offset into the staged arrays (16-byte slots)
+            const uint32_t jo = u == 0 ? (quad << 4) & 0xff0u : (quad >> (8 * u - 4)) & 0xff0u;
+            const uint32_t j = jo >> 4;
+            const float4 g0 = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(s.g0) + jo);
+            const float4 g1 = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(s.g1) + jo);
+            const float dx = g0.x - fpx, dy = g0.y - fpy;
+            // log2 of exp(power) with power = -(A dx^2 + 2B dx dy + C dy^2)/2
+            const float p2 = __builtin_fmaf(dx, __builtin_fmaf(g0.z, dx, g0.w * dy), g1.x * dy * dy);
+            const float alpha = fminf(kAlphaMax, g1.y * __builtin_amdgcn_exp2f(p2));
+            // composited or stopping: an entry of a running pixel with power
+            // <= 0 and alpha >= 1/255.  The decisions are wave masks
+            // (compares straight into scalar registers, combined there)
+            const uint64_t hitm = __builtin_amdgcn_ballot_w64(!(p2 > 0.0f)) &
+                                  __builtin_amdgcn_ballot_w64(alpha >= kAlphaMin) & ~done;
+            const float Tn = T * (1.0f - alpha);
+            // T stays above 1e-4 (Tn is never NaN)
+            const uint64_t keepm = __builtin_amdgcn_ballot_w64(Tn >= kTMin);
+            const bool hit = __builtin_amdgcn_inverse_ballot_w64(hitm);
+            const bool inc = __builtin_amdgcn_inverse_ballot_w64(hitm & keepm);
+            const bool stop = __builtin_amdgcn_inverse_ballot_w64(hitm & ~keepm);
+            const float w = inc ? alpha * T : 0.0f;
+            const float4 c = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(s.col) + jo);
+            cr = __builtin_fmaf(w, c.x, cr);
+            cg = __builtin_fmaf(w, c.y, cg);
+            cb = __builtin_fmaf(w, c.z, cb);
+            T = inc ? Tn : T;
+            done |= hitm & ~keepm;
+            if (COUNT) {
+                n_hit += hit ? 1u : 0u;
+                if (stop) stop_pos = b + j;
             }
-        } else {
-            // list slots are read four at a time (one aligned 32-bit LDS load
-            // per four entries, each slot's byte offset taken with constant
-            // shifts): three entries in four wait for one LDS round trip (the
-            // staged record) instead of two.  The walk runs to the wave's
-            // longest list rounded up to four: the slots past every list's
-            // end hold the sentinel (alpha 0)
-            bool stopped = false;
-            for (uint32_t e = 0; e < n_run && !stopped; e += 4) {
-              const uint32_t quad = *reinterpret_cast<const uint32_t *>(&s.list[my_list][e]);
+            if (CAPTURE) {
+                const float dep = g1.z;
+                d0 = (inc && !pivot) ? dep : d0;
+                pivot = pivot || inc;
+                const float dd = dep - d0;
+                sw += w;
+                s1 = __builtin_fmaf(w, dd, s1);
+                s2 = __builtin_fmaf(w * dd, dd, s2);
+                // the pixel composites the Gaussian (w = alpha T > 0); the
+                // lanes of a group write the same flag, in the slot's
+                // staged record (no index to form)
+                if (inc) *reinterpret_cast<float *>(reinterpret_cast<char *>(s.g1) + jo + 12) = 1.0f;
+                if (CONTRIB) {
+                    // max weight over the group's 16 lanes (one Gaussian)
+                    float mw = w;
 #pragma unroll
-              for (int u = 0; u < 4; ++u) {
-                // byte offset into the staged arrays (16-byte slots)
-                const uint32_t jo = u == 0 ? (quad << 4) & 0xff0u : (quad >> (8 * u - 4)) & 0xff0u;
-                const uint32_t j = jo >> 4;
-                const float4 g0 = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(s.g0) + jo);
-                const float4 g1 = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(s.g1) + jo);
-                const float dx = g0.x - fpx, dy = g0.y - fpy;
-                // log2 of exp(power) with power = -(A dx^2 + 2B dx dy + C dy^2)/2
-                const float p2 = __builtin_fmaf(dx, __builtin_fmaf(g0.z, dx, g0.w * dy), g1.x * dy * dy);
-                const float alpha = fminf(kAlphaMax, g1.y * __builtin_amdgcn_exp2f(p2));
-                // composited or stopping: an entry of a running pixel with power
-                // <= 0 and alpha >= 1/255.  The decisions are wave masks
-                // (compares straight into scalar registers, combined there)
-                const uint64_t hitm = __builtin_amdgcn_ballot_w64(!(p2 > 0.0f)) &
-                                      __builtin_amdgcn_ballot_w64(alpha >= kAlphaMin) & ~done;
-                const float Tn = T * (1.0f - alpha);
-                // T stays above 1e-4 (Tn is never NaN)
-                const uint64_t keepm = __builtin_amdgcn_ballot_w64(Tn >= kTMin);
-                const bool hit = __builtin_amdgcn_inverse_ballot_w64(hitm);
-                const bool inc = __builtin_amdgcn_inverse_ballot_w64(hitm & keepm);
-                const bool stop = __builtin_amdgcn_inverse_ballot_w64(hitm & ~keepm);
-                const float w = inc ? alpha * T : 0.0f;
-                const float4 c = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(s.col) + jo);
-                cr = __builtin_fmaf(w, c.x, cr);
-                cg = __builtin_fmaf(w, c.y, cg);
-                cb = __builtin_fmaf(w, c.z, cb);
-                T = inc ? Tn : T;
-                done |= hitm & ~keepm;
-                if (COUNT) {
-                    n_hit += hit ? 1u : 0u;
-                    if (stop) stop_pos = b + j;
+                    for (int o = 8; o >= 1; o >>= 1) mw = fmaxf(mw, __shfl_xor(mw, o));
+                    if ((lane & 15) == 0 && mw > 0.0f)
+                        atomicMax(reinterpret_cast<unsigned int *>(a.contrib + s.idx[j]),
+                                  __float_as_uint(mw));
                 }
-                if (CAPTURE) {
-                    const float dep = g1.z;
-                    d0 = (inc && !pivot) ? dep : d0;
-                    pivot = pivot || inc;
-                    const float dd = dep - d0;
-                    sw += w;
-                    s1 = __builtin_fmaf(w, dd, s1);
-                    s2 = __builtin_fmaf(w * dd, dd, s2);
-                    // the pixel composites the Gaussian (w = alpha T > 0); the
-                    // lanes of a group write the same flag, in the slot's
-                    // staged record (no index to form)
-                    if (inc) *reinterpret_cast<float *>(reinterpret_cast<char *>(s.g1) + jo + 12) = 1.0f;
-                    if (CONTRIB) {
-                        // max weight over the group's 16 lanes (one Gaussian)
-                        float mw = w;
-#pragma unroll
-                        for (int o = 8; o >= 1; o >>= 1) mw = fmaxf(mw, __shfl_xor(mw, o));
-                        if ((lane & 15) == 0 && mw > 0.0f)
-                            atomicMax(reinterpret_cast<unsigned int *>(a.contrib + s.idx[j]),
-                                      __float_as_uint(mw));
-                    }
-                }
-                if (done == ~0ull) {
-                    stopped = true;
-                    break;
-                }
-              }
             }
+            if (done == ~0ull) {
+                stopped = true;
+                break;
+            }
+          }
         }
         __syncthreads();
         if (CAPTURE && a.g_flag && tid < kBatch && kb < range.y && s.g1[tid].w != 0.0f)
@@ -571,11 +770,11 @@ __device__ __attribute__((always_inline)) inline void blend_block(const BlendArg
 }
 
 // Eight waves per SIMD (64 VGPRs); the capture variants, which carry the
-// Eq. 1/2 sums as well, at seven (72 VGPRs) so that nothing spills to
-// scratch.
+// Eq. 1/2 sums as well, at seven (72 VGPRs).  What is left to spill is spilled
+// once per filling of a quadrant block, never in a walk.
 template <bool CAPTURE, bool CONTRIB, bool COUNT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CAPTURE ? 7 : 8))) void blend_kernel(BlendArgs a) {
-    __shared__ BlendLds s;
+    __shared__ BlendLds<COUNT> s;
     // block roles (block-uniform): with a split count ns, the first
     // nq = 4 ceil8(ns) blocks take the quadrants of the first ns tiles of the
     // blend order, the rest shift down by nq - ns; then the tiles, then (TGS

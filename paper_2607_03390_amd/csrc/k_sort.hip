@@ -344,9 +344,19 @@ __global__ __launch_bounds__(kSortThreads) void sort_downsweep_kernel(
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t K = MODE == kFirst ? n_host : key_count(n_dev, n_host);
-    const uint32_t part = blockIdx.x;
+    const uint32_t npa = (K + kTile - 1) / kTile;
+    // Blocks are dealt to the eight XCDs in turn; each XCD takes a run of
+    // consecutive partitions.  A partition writes runs of 20-40 keys per digit
+    // that neither begin nor end on a cache line, and the next partition's run
+    // continues each of them: written through the same L2 the two halves of
+    // a line leave as one full line, through two they leave as partial lines
+    // (2.27G keys at 8 + 7 bits: 19.0 -> 10.5 ms per pass; 5.0M keys, which
+    // the last-level cache holds: 21.2 -> 21.1 us).
+    const uint32_t per_xcd = npa ? (npa + 7) / 8 : 1u;
+    if ((blockIdx.x >> 3) >= per_xcd) return;
+    const uint32_t part = (blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);
     const uint32_t base = part * kTile;
-    const uint32_t c_mine = part / chunk_len((K + kTile - 1) / kTile);
+    const uint32_t c_mine = part / chunk_len(npa);
     // digit tid: its total over all chunks and its sum over the chunks before this one
     uint64_t tot = 0, pre = 0, wtot = 0, wpre = 0;
 #pragma unroll
@@ -371,7 +381,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_downsweep_kernel(
         (void)block_exclusive_scan256<uint64_t>(wtot, s_scan64, &n_keys);
         publish_counters(io, n_keys, s_wh);
     }
-    if (base >= K) return;   // block-uniform
+    if (part >= npa) return;   // block-uniform
     // issue every global load of the block before the first barrier
     const uint32_t wbase = base + (uint32_t)wave * (64u * IPT);
     const uint64_t lt_mask = (1ull << lane) - 1ull;
@@ -568,7 +578,8 @@ void one_pass(const uint32_t *n_dev, uint32_t n_max, int shift, int nbits, const
             ki, vi, nd, n_max, shift, nbits, np, io, table, table + (size_t)np * kRadix);
     sort_colscan_kernel<<<tables * 16 * kChunks, 256, 0, st>>>(nd, n_max, kSortThreads * IPT, np,
                                                                 table, chunk_sums);
-    sort_downsweep_kernel<IPT, MODE, KT><<<np, kSortThreads, 0, st>>>(ki, vi, ko, vo, nd, n_max, shift,
+    // whole rounds of eight blocks (one per XCD)
+    sort_downsweep_kernel<IPT, MODE, KT><<<(np + 7) / 8 * 8, kSortThreads, 0, st>>>(ki, vi, ko, vo, nd, n_max, shift,
                                                                   nbits, np, table, chunk_sums, io);
 }
 

@@ -71,9 +71,11 @@ struct DupIo {
     const int *sel_cols;
     int TX;
     int n_tiles;
-    uint2 *ranges;   // cleared by the first kernel of the emission
-    uint32_t *rows;  // optional: digit counts of each block's keys for the tile sort
-    int row_bits;    // width of that digit (key bits [0, row_bits))
+    uint2 *ranges;       // cleared by the emission, as the tiles' lengths
+    uint32_t *tile_len;  // (packed keys)
+    uint32_t *rows;  // optional: counts of the low digit in each block's keys
+    int lo_bits;     // packed keys: width of the low digit
+    int index_bits;  // packed keys: where the high digit starts in the payload
 };
 
 // Window of the Gaussians owning output positions [P0, P1) (P0 a multiple
@@ -91,13 +93,13 @@ __device__ inline void dup_window(const DupIo &io, uint32_t P0, uint32_t P1, uin
 
 // Owners of the output positions [P0, P1) by a block of NT threads: s_off[k]
 // / s_g[k] = start and Gaussian index of window entry k (those starting
-// before P1), s_owner[i] = the window entry owning position P0 + i.  The
-// window is read in one step (every load in flight at once).  Ends with a
-// barrier.
+// before P1), own[i] = the window entry owning position P0 + kPer tid + i
+// (kPer consecutive positions per thread; past P1: the last entry).  The
+// window is read in one step (every load in flight at once).
 template <int KD, int NT>
 __device__ inline void dup_owners(const DupIo &io, uint32_t P0, uint32_t P1, uint32_t K,
-                                  uint32_t V, int *s_owner, uint32_t *s_off, uint32_t *s_g,
-                                  int *s_wmax) {
+                                  uint32_t V, int *s_mark, uint32_t *s_off, uint32_t *s_g,
+                                  int *s_wmax, int (&own)[KD / NT]) {
     static_assert(KD % NT == 0 && KD % kKeyBlock == 0, "whole steps and key blocks");
     constexpr int kPer = KD / NT;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -111,7 +113,7 @@ __device__ inline void dup_owners(const DupIo &io, uint32_t P0, uint32_t P1, uin
         o[i] = io.offs[j0 + kc];
         g[i] = io.didx[j0 + kc];
     }
-    for (int k = tid; k < KD; k += NT) s_owner[k] = -1;
+    for (int k = tid; k < KD; k += NT) s_mark[k] = -1;
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
@@ -119,16 +121,16 @@ __device__ inline void dup_owners(const DupIo &io, uint32_t P0, uint32_t P1, uin
         if ((uint32_t)k < nw && (k == 0 || o[i] < P1)) {
             s_off[k] = o[i];
             s_g[k] = g[i];
-            s_owner[k == 0 ? 0 : (int)(o[i] - P0)] = k;
+            s_mark[k == 0 ? 0 : (int)(o[i] - P0)] = k;
         }
     }
     __syncthreads();
-    // inclusive max-scan of the marks: kPer consecutive entries per thread
-    int v[kPer], m = -1;
+    // inclusive max-scan of the marks
+    int m = -1;
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
-        m = max(m, s_owner[kPer * tid + i]);
-        v[i] = m;
+        m = max(m, s_mark[kPer * tid + i]);
+        own[i] = m;
     }
     int inc = m;
 #pragma unroll
@@ -142,75 +144,102 @@ __device__ inline void dup_owners(const DupIo &io, uint32_t P0, uint32_t P1, uin
     __syncthreads();
     for (int w = 0; w < wave; ++w) ex = max(ex, s_wmax[w]);
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) s_owner[kPer * tid + i] = max(v[i], ex);
-    __syncthreads();
+    for (int i = 0; i < kPer; ++i) own[i] = max(own[i], ex);
 }
 
-// Block b emits output keys [1024 b, 1024 b + 1024), four per thread at
-// consecutive positions across the block (coalesced stores), whatever the
-// Gaussians' key counts: a Gaussian spanning thousands of tiles is spread
-// over many blocks instead of holding one wave.  Owners of the positions
-// come from the key-block table and the window of Gaussians starting inside
-// the block (dup_owners).  Past the key capacity (cnt->n_sorted == 0 with
-// keys) nothing is emitted: the host grows the buffers and renders the
-// frame again.  With io.rows, the block also counts its keys' first
-// tile-sort digit into row blockIdx.x (LDS counters per wave), so that the
-// sort's first pass needs no counting launch of its own.
+// Block b emits output keys [1024 b, 1024 b + 1024), four consecutive ones per
+// thread (one 16-byte store of indices or payloads, one store of tile ids or
+// digits), whatever the Gaussians' key counts: a Gaussian spanning thousands
+// of tiles is spread over many blocks instead of holding one wave.  Owners
+// of the positions come from the key-block table and the window of Gaussians
+// starting inside the block (dup_owners).  A thread finds the tile of its
+// first key from the rank inside the owner's rectangle; the next ones of the
+// same owner follow it along the row.  Past the key capacity
+// (cnt->n_sorted == 0 with keys) nothing is emitted: the host grows the
+// buffers and renders the frame again.  With io.rows, the block also counts
+// its keys' low digits into row blockIdx.x (LDS counters per wave), so that
+// the tile sort's first pass needs no counting launch of its own.
 constexpr int kDupKeys = kKeyBlock;
 
+template <bool PACKED>
 __global__ __launch_bounds__(256) void duplicate_kernel(DupIo io, uint32_t *tkey, uint32_t *tval) {
-    __shared__ int s_owner[kDupKeys];
+    __shared__ int s_mark[kDupKeys];
     __shared__ uint32_t s_off[kDupKeys];
     __shared__ uint32_t s_g[kDupKeys];
     __shared__ int s_wmax[4];
     __shared__ uint32_t s_hist[4][256];
     const int tid = threadIdx.x;
-    for (int t = blockIdx.x * blockDim.x + tid; t < io.n_tiles; t += gridDim.x * blockDim.x)
+    for (int t = blockIdx.x * blockDim.x + tid; t < io.n_tiles; t += gridDim.x * blockDim.x) {
         io.ranges[t] = make_uint2(0u, 0u);
+        if (PACKED) io.tile_len[t] = 0u;
+    }
     const uint32_t V = io.cnt->n_visible, K = io.cnt->n_sorted;
     const uint32_t P0 = blockIdx.x * (uint32_t)kDupKeys;
     if (K == 0u || P0 >= K) return;   // block-uniform
-    if (io.rows) {
+    if (PACKED && io.rows) {
 #pragma unroll
         for (int w = 0; w < 4; ++w) s_hist[w][tid] = 0u;   // ordered by dup_owners' barriers
     }
     const uint32_t P1 = K - P0 < (uint32_t)kDupKeys ? K : P0 + kDupKeys;
-    dup_owners<kDupKeys, 256>(io, P0, P1, K, V, s_owner, s_off, s_g, s_wmax);
-    // positions past the keys take the last key's owner (no branch before
-    // the stores, so every rectangle load is in flight together)
     constexpr int kPer = kDupKeys / 256;
-    uint32_t g[kPer], r[kPer];
+    static_assert(kPer == 4, "four keys per 16-byte store");
+    int own[kPer];
+    dup_owners<kDupKeys, 256>(io, P0, P1, K, V, s_mark, s_off, s_g, s_wmax, own);
+    // positions past the keys take the last key's (no branch before the
+    // stores, so every rectangle load is in flight together)
+    const uint32_t p = P0 + (uint32_t)(kPer * tid);
+    uint32_t g[kPer], r[kPer], key[kPer];
     ushort4 rc[kPer];
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
-        const uint32_t p = P0 + (uint32_t)(tid + 256 * k), pc = p < P1 ? p : P1 - 1u;
-        const int w = s_owner[pc - P0];
-        g[k] = s_g[w];
-        r[k] = pc - s_off[w];
+        const uint32_t pc = p + k < P1 ? p + k : P1 - 1u;
+        g[k] = s_g[own[k]];
+        r[k] = pc - s_off[own[k]];
         rc[k] = io.rect[g[k]];
     }
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
-        const uint32_t p = P0 + (uint32_t)(tid + 256 * k);
         int tx, ty;
         key_tile_xy(r[k], rc[k], io.rowpre, io.sel_cols, io.TX, tx, ty);
-        if (p < P1) {
-            const uint32_t key = (uint32_t)(ty * io.TX + tx);
-            tkey[p] = key;
-            tval[p] = g[k];
-            if (io.rows) atomicAdd(&s_hist[tid >> 6][key & ((1u << io.row_bits) - 1u)], 1u);
+        key[k] = (uint32_t)(ty * io.TX + tx);
+    }
+    const uint32_t lmask = PACKED ? (1u << io.lo_bits) - 1u : 0u;
+    uint32_t val[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k)
+        val[k] = PACKED ? g[k] | (key[k] >> io.lo_bits) << (io.index_bits & 31) : g[k];
+    if (p + kPer <= P1) {
+        *reinterpret_cast<uint4 *>(tval + p) = make_uint4(val[0], val[1], val[2], val[3]);
+        if (PACKED)
+            reinterpret_cast<uint32_t *>(tkey)[p / 4] = (key[0] & lmask) | (key[1] & lmask) << 8 |
+                                                        (key[2] & lmask) << 16 | (key[3] & lmask) << 24;
+        else
+            *reinterpret_cast<uint4 *>(tkey + p) = make_uint4(key[0], key[1], key[2], key[3]);
+    } else {
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            if (p + k < P1) {
+                tval[p + k] = val[k];
+                if (PACKED) reinterpret_cast<uint8_t *>(tkey)[p + k] = (uint8_t)(key[k] & lmask);
+                else tkey[p + k] = key[k];
+            }
         }
     }
-    if (io.rows) {
+    if (PACKED && io.rows) {
+#pragma unroll
+        for (int k = 0; k < kPer; ++k)
+            if (p + k < P1) atomicAdd(&s_hist[tid >> 6][key[k] & lmask], 1u);
         __syncthreads();
         io.rows[(size_t)blockIdx.x * 256 + tid] = s_hist[0][tid] + s_hist[1][tid] + s_hist[2][tid] +
                                                   s_hist[3][tid];
     }
 }
 
-__global__ __launch_bounds__(256) void ranges_zero_kernel(int n_tiles, uint2 *ranges) {
+__global__ __launch_bounds__(256) void ranges_zero_kernel(int n_tiles, uint2 *ranges, uint32_t *tile_len) {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < n_tiles) ranges[t] = make_uint2(0u, 0u);
+    if (t >= n_tiles) return;
+    ranges[t] = make_uint2(0u, 0u);
+    if (tile_len) tile_len[t] = 0u;
 }
 
 // Four consecutive sorted keys per thread (one 16-byte load) and the key on
@@ -248,9 +277,15 @@ __global__ __launch_bounds__(256) void ranges_kernel(const Counters *cnt, const 
     }
 }
 
-__global__ __launch_bounds__(1024) void order_tiles_kernel(OrderK o) {
-    __shared__ uint32_t s_cnt[order_lds_words(1024)];
-    order_tiles_block<1024, true>(o, s_cnt);
+__global__ __launch_bounds__(256) void order_tiles_kernel(OrderK o) {
+    __shared__ uint32_t s_cnt[order_lds_words(256)];
+    order_tiles_share<256>(
+        o, o.n_dev ? (int)*o.n_dev : o.n_host, (int)blockIdx.x, (int)gridDim.x, s_cnt,
+        [&](int i) { return o.tile_in ? o.tile_in[i] : i; },
+        [&](int t) {
+            const uint2 r = o.ranges[t];
+            return length_bucket(r.y - r.x);
+        });
 }
 
 }  // namespace
@@ -258,16 +293,18 @@ __global__ __launch_bounds__(1024) void order_tiles_kernel(OrderK o) {
 void launch_duplicate(int n, uint32_t cap, const Counters *cnt, const uint32_t *didx,
                       const uint32_t *offs, const uint32_t *kfirst, const ushort4 *rect,
                       const uint32_t *rowpre, const int *sel_cols, int TX, int n_tiles,
-                      uint32_t *tkey, uint32_t *tval, uint2 *ranges, uint32_t *rows, int row_bits,
-                      hipStream_t st) {
+                      const TileSortPlan &tp, uint32_t *tkey, uint32_t *tval, uint2 *ranges,
+                      uint32_t *tile_len, uint32_t *rows, hipStream_t st) {
     if (n <= 0 || cap == 0) {
-        ranges_zero_kernel<<<(n_tiles + 255) / 256, 256, 0, st>>>(n_tiles, ranges);
+        ranges_zero_kernel<<<(n_tiles + 255) / 256, 256, 0, st>>>(n_tiles, ranges,
+                                                                 tp.packed ? tile_len : nullptr);
         return;
     }
     const uint32_t blocks = (cap + kDupKeys - 1) / kDupKeys;
     const DupIo io{cnt, didx, offs, kfirst, rect, rowpre, sel_cols, TX, n_tiles, ranges,
-                   row_bits > 0 ? rows : nullptr, row_bits};
-    duplicate_kernel<<<blocks, 256, 0, st>>>(io, tkey, tval);
+                   tile_len, rows, tp.lo, tp.index_bits};
+    if (tp.packed) duplicate_kernel<true><<<blocks, 256, 0, st>>>(io, tkey, tval);
+    else duplicate_kernel<false><<<blocks, 256, 0, st>>>(io, tkey, tval);
 }
 
 void launch_ranges(uint32_t cap, const Counters *cnt, const uint32_t *keys, uint2 *ranges,
@@ -280,7 +317,7 @@ void launch_ranges(uint32_t cap, const Counters *cnt, const uint32_t *keys, uint
 }
 
 void launch_order_tiles(const OrderK &o, hipStream_t st) {
-    if (o.n_host > 0) order_tiles_kernel<<<1, 1024, 0, st>>>(o);
+    if (o.n_host > 0) order_tiles_kernel<<<kOrderShares, 256, 0, st>>>(o);
 }
 
 }  // namespace tgs

@@ -37,14 +37,13 @@
 //    where the Gaussian's tile keys start, and the owner of every 1024-key
 //    block of the emission.  It publishes the frame's counters to the host.
 #include "match.h"
+#include "radix.h"
 #include "tgs_internal.h"
 
 namespace tgs {
 
 namespace {
 
-constexpr int kSortThreads = 256;
-constexpr int kRadix = 256;
 // Keys per thread: partitions of 256 * IPT keys.  Large partitions for large
 // sorts (fewer counts to scan), small ones for small sorts (enough blocks to
 // fill the chip).
@@ -59,31 +58,6 @@ enum { kPlain = 0, kFirst = 1, kLast = 2 };
 
 __device__ inline uint32_t key_count(const uint32_t *n_dev, uint32_t n_host) {
     return n_dev ? *n_dev : n_host;
-}
-
-__device__ inline uint32_t sat32(uint64_t v) { return v > 0xffffffffull ? 0xffffffffu : (uint32_t)v; }
-
-template <typename T>
-__device__ inline T block_exclusive_scan256(T v, T *s_wave, T *total = nullptr) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    T inc = v;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const T o = __shfl_up(inc, d);
-        if (lane >= d) inc += o;
-    }
-    if (lane == 63) s_wave[wave] = inc;
-    __syncthreads();
-    T off = 0, tot = 0;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        const T x = s_wave[w];
-        if (w < wave) off += x;
-        tot += x;
-    }
-    __syncthreads();
-    if (total) *total = tot;
-    return off + inc - v;
 }
 
 // Operands of the first and last depth-sort passes.
@@ -182,19 +156,11 @@ __global__ __launch_bounds__(kSortThreads) void sort_upsweep_kernel(
     }
 }
 
-// The partitions holding keys are cut into kChunks chunks of L consecutive
-// partitions.  One block per (table, chunk, group of 16 digits): exclusive
+// One block per (table, chunk, group of 16 digits): exclusive
 // scan, within the chunk, of each digit's counts (table 0) or weights
 // (table 1), in place, and the chunk's digit sums in chunk_sums[c * 256 + d]
 // (saturated to 32 bits).  A row of 16 digits is one 64-byte line, so every
 // load uses whole lines.  The downsweep adds the sums of earlier chunks.
-constexpr int kChunks = 16;
-
-__device__ inline uint32_t chunk_len(uint32_t npa) {
-    const uint32_t L = (npa + kChunks - 1) / kChunks;
-    return L ? L : 1u;
-}
-
 __global__ __launch_bounds__(256) void sort_colscan_kernel(const uint32_t *n_dev, uint32_t n_host,
                                                            uint32_t tile, uint32_t np,
                                                            uint32_t *counts, uint32_t *chunk_sums) {
@@ -345,16 +311,8 @@ __global__ __launch_bounds__(kSortThreads) void sort_downsweep_kernel(
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t K = MODE == kFirst ? n_host : key_count(n_dev, n_host);
     const uint32_t npa = (K + kTile - 1) / kTile;
-    // Blocks are dealt to the eight XCDs in turn; each XCD takes a run of
-    // consecutive partitions.  A partition writes runs of 20-40 keys per digit
-    // that neither begin nor end on a cache line, and the next partition's run
-    // continues each of them: written through the same L2 the two halves of
-    // a line leave as one full line, through two they leave as partial lines
-    // (2.27G keys at 8 + 7 bits: 19.0 -> 10.5 ms per pass; 5.0M keys, which
-    // the last-level cache holds: 21.2 -> 21.1 us).
-    const uint32_t per_xcd = npa ? (npa + 7) / 8 : 1u;
-    if ((blockIdx.x >> 3) >= per_xcd) return;
-    const uint32_t part = (blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);
+    uint32_t part;
+    if (!xcd_partition(blockIdx.x, npa, part)) return;
     const uint32_t base = part * kTile;
     const uint32_t c_mine = part / chunk_len(npa);
     // digit tid: its total over all chunks and its sum over the chunks before this one
@@ -561,23 +519,19 @@ inline uint32_t n_partitions(uint32_t K, int ipt) {
     return np ? np : 1u;
 }
 
-// counted: the count table already holds the pass's digit counts (one row
-// per partition, written by the key emission), so it has no counting launch.
 template <int IPT, int MODE, typename KT = uint32_t>
 void one_pass(const uint32_t *n_dev, uint32_t n_max, int shift, int nbits, const uint32_t *ki,
               const uint32_t *vi, uint32_t *ko, uint32_t *vo, uint32_t *scratch, const DepthIo &io,
-              bool counted, hipStream_t st) {
+              hipStream_t st) {
     // at least one block: the last depth pass always publishes the counters
     const uint32_t np = n_partitions(n_max, IPT);
     uint32_t *chunk_sums = scratch;                 // [2][kChunks][256]
     uint32_t *table = sort_count_rows(scratch);     // [2][np][256]
     const uint32_t *nd = MODE == kFirst ? nullptr : n_dev;
     const int tables = MODE == kLast ? 2 : 1;
-    if (!counted)
-        sort_upsweep_kernel<IPT, MODE><<<np, kSortThreads, 0, st>>>(
-            ki, vi, nd, n_max, shift, nbits, np, io, table, table + (size_t)np * kRadix);
-    sort_colscan_kernel<<<tables * 16 * kChunks, 256, 0, st>>>(nd, n_max, kSortThreads * IPT, np,
-                                                                table, chunk_sums);
+    sort_upsweep_kernel<IPT, MODE><<<np, kSortThreads, 0, st>>>(
+        ki, vi, nd, n_max, shift, nbits, np, io, table, table + (size_t)np * kRadix);
+    launch_colscan(nd, n_max, kSortThreads * IPT, np, tables, table, chunk_sums, st);
     // whole rounds of eight blocks (one per XCD)
     sort_downsweep_kernel<IPT, MODE, KT><<<(np + 7) / 8 * 8, kSortThreads, 0, st>>>(ki, vi, ko, vo, nd, n_max, shift,
                                                                   nbits, np, table, chunk_sums, io);
@@ -587,17 +541,16 @@ template <int IPT>
 void depth_passes(uint32_t n, const uint32_t *dkey, uint32_t *k_a, uint32_t *v_a, uint32_t *k_b,
                   uint32_t *v_b, uint32_t *scratch, const DepthIo &io, hipStream_t st) {
     const uint32_t *n_vis = &io.cnt->n_visible;
-    one_pass<IPT, kFirst>(nullptr, n, 0, 8, dkey, nullptr, k_a, v_a, scratch, io, false, st);
-    one_pass<IPT, kPlain>(n_vis, n, 8, 8, k_a, v_a, k_b, v_b, scratch, io, false, st);
-    one_pass<IPT, kPlain>(n_vis, n, 16, 8, k_b, v_b, k_a, v_a, scratch, io, false, st);
+    one_pass<IPT, kFirst>(nullptr, n, 0, 8, dkey, nullptr, k_a, v_a, scratch, io, st);
+    one_pass<IPT, kPlain>(n_vis, n, 8, 8, k_a, v_a, k_b, v_b, scratch, io, st);
+    one_pass<IPT, kPlain>(n_vis, n, 16, 8, k_b, v_b, k_a, v_a, scratch, io, st);
     // kept depths are positive (above the near plane): the sign bit is zero
-    one_pass<IPT, kLast>(n_vis, n, 24, 7, k_a, v_a, nullptr, v_b, scratch, io, false, st);
+    one_pass<IPT, kLast>(n_vis, n, 24, 7, k_a, v_a, nullptr, v_b, scratch, io, st);
 }
 
 template <int IPT, typename KT = uint32_t>
 void plain_passes(const uint32_t *n_dev, uint32_t n_max, int begin_bit, int bits, uint32_t *ki,
-                  uint32_t *vi, uint32_t *ko, uint32_t *vo, uint32_t *scratch, bool counted,
-                  hipStream_t st) {
+                  uint32_t *vi, uint32_t *ko, uint32_t *vo, uint32_t *scratch, hipStream_t st) {
     const DepthIo none{};
     // digits of (nearly) equal width: fewer runs per partition in the widest
     // pass, so its scattered writes come in longer pieces
@@ -605,8 +558,7 @@ void plain_passes(const uint32_t *n_dev, uint32_t n_max, int begin_bit, int bits
     int shift = begin_bit;
     for (int p = 0; p < passes; ++p) {
         const int nb = bits / passes + (p < bits % passes ? 1 : 0);
-        one_pass<IPT, kPlain, KT>(n_dev, n_max, shift, nb, ki, vi, ko, vo, scratch, none,
-                                  counted && p == 0, st);
+        one_pass<IPT, kPlain, KT>(n_dev, n_max, shift, nb, ki, vi, ko, vo, scratch, none, st);
         shift += nb;
         uint32_t *t = ki; ki = ko; ko = t;
         t = vi; vi = vo; vo = t;
@@ -625,11 +577,17 @@ size_t sort_scratch_words(uint32_t max_keys) {
     return (size_t)2 * kChunks * kRadix + (size_t)2 * kRadix * np;
 }
 
+size_t tile_sort_scratch_words(uint32_t max_keys) {
+    // one count table, with a partition more per low digit in the second pass
+    const size_t np = n_partitions(max_keys, kIptSmall);
+    return (size_t)2 * kChunks * kRadix + kRadix * (np + kRadix);
+}
+
 uint32_t *sort_count_rows(uint32_t *scratch) { return scratch + 2 * kChunks * kRadix; }
 
-int sort_first_digit_bits(int bits) {
-    const int passes = sort_passes_for_bits(bits);
-    return passes > 0 ? bits / passes + (bits % passes ? 1 : 0) : 0;
+void launch_colscan(const uint32_t *n_dev, uint32_t n_host, uint32_t tile, uint32_t np, int tables,
+                    uint32_t *table, uint32_t *sums, hipStream_t st) {
+    sort_colscan_kernel<<<tables * 16 * kChunks, 256, 0, st>>>(n_dev, n_host, tile, np, table, sums);
 }
 
 // Items per thread of a plain sort: by the expected count (the grid covers
@@ -639,34 +597,23 @@ static int plain_ipt(uint32_t n_max, uint32_t n_hint, int begin_bit, int bits) {
     return begin_bit + bits <= 16 ? kIptLarge16 : kIptLarge;
 }
 
-// Counted rows are taken where a partition is one block of the emission
-// (1024 keys).  Larger partitions could sum several rows, but their column
-// scan over five times the rows cost more than the counting launch it
-// replaces (room full frame: 4.8 -> 8.5 us against 5.3 us).
-bool sort_takes_rows(uint32_t n_max, uint32_t n_hint, int begin_bit, int bits) {
-    static_assert(kKeyBlock == kSortThreads * kIptSmall, "a counted row is a small partition");
-    if (n_max <= 1 || sort_passes_for_bits(bits) <= 0) return false;
-    return plain_ipt(n_max, n_hint, begin_bit, bits) == kIptSmall;
-}
-
 int launch_sort_u32(const uint32_t *n_dev, uint32_t n_max, uint32_t n_hint, int begin_bit,
                     int bits, uint32_t *keys, uint32_t *vals, uint32_t *keys_alt,
-                    uint32_t *vals_alt, uint32_t *scratch, bool counted, hipStream_t st) {
+                    uint32_t *vals_alt, uint32_t *scratch, hipStream_t st) {
     const int passes = sort_passes_for_bits(bits);
     if (n_max <= 1 || passes <= 0) return 0;
-    counted = counted && sort_takes_rows(n_max, n_hint, begin_bit, bits);
     switch (plain_ipt(n_max, n_hint, begin_bit, bits)) {
         case kIptSmall:
             plain_passes<kIptSmall>(n_dev, n_max, begin_bit, bits, keys, vals, keys_alt, vals_alt,
-                                    scratch, counted, st);
+                                    scratch, st);
             break;
         case kIptLarge16:
             plain_passes<kIptLarge16, uint16_t>(n_dev, n_max, begin_bit, bits, keys, vals, keys_alt,
-                                                vals_alt, scratch, counted, st);
+                                                vals_alt, scratch, st);
             break;
         default:
             plain_passes<kIptLarge>(n_dev, n_max, begin_bit, bits, keys, vals, keys_alt, vals_alt,
-                                    scratch, counted, st);
+                                    scratch, st);
             break;
     }
     return passes & 1;

@@ -1,5 +1,6 @@
-// Blend order of the tiles to rasterise, run by the standalone order kernel
-// or, in frames with a per-tile sort, by the first block of that launch.
+// Blend order of the tiles to rasterise, run by the first block of the tile
+// sort's last launch or, on grids that take the general sort, by a kernel of
+// its own.
 #pragma once
 
 #include "match.h"
@@ -14,11 +15,7 @@ namespace tgs {
 // within a bucket changes only scheduling, never a result; the split set is
 // a union of whole buckets.
 // Bucket of a list length: floor(log2(len)) + 1, 0 for an empty list.
-__device__ inline uint32_t length_bucket(const uint2 *ranges, int t) {
-    const uint2 r = ranges[t];
-    const uint32_t len = r.y - r.x;
-    return len ? 32u - (uint32_t)__clz(len) : 0u;
-}
+__device__ inline uint32_t length_bucket(uint32_t len) { return len ? 32u - (uint32_t)__clz(len) : 0u; }
 
 // Length bucket from which a frame of n_keys keys splits its tiles, at most
 // most: lists of at least the keys that 1024 evenly loaded blocks would each
@@ -39,9 +36,9 @@ __device__ inline int split_bucket_for(uint32_t n_keys, int most) {
 }
 
 constexpr int kOrderBuckets = 33;
-// LDS words of order_tiles_block<NT, ...>: bucket counters per wave (at
-// most).
-constexpr int order_lds_words(int nt) { return (nt / 64) * kOrderBuckets; }
+// LDS words of order_tiles_share<NT>: two copies of the bucket counters per
+// wave, twice.
+constexpr int order_lds_words(int nt) { return 4 * (nt / 64) * kOrderBuckets; }
 
 // Ranks N items per lane against running bucket counters wc[33] (in
 // order: item k before item k + 1, lanes in order): lanes with equal
@@ -70,35 +67,18 @@ __device__ inline void wave_bucket_rank(uint32_t *wc, const uint32_t (&b)[N], co
     for (int k = 0; k < N; ++k) rank[k] = __shfl(base[k], leader[k]) + (uint32_t)__popcll(pm[k] & lt);
 }
 
-// Bucket totals of the per-wave counts wc[w][b] (kWaves rows), then each
-// wave's start in every bucket (buckets longest first, waves in order), in
-// place; the split count and the longest bucket for the host.  Run by the
-// first 64 threads between two barriers.
-template <int kWaves>
-__device__ inline void order_bucket_starts(const OrderK &o, uint32_t *s_cnt) {
-    const int tid = threadIdx.x;
-    // lane l holds bucket 32 - l
-    const int b = 32 - tid;
-    uint32_t c = 0;
-    if (b >= 0) {
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) c += s_cnt[w * kOrderBuckets + b];
-    }
+// First place of bucket 32 - tid in the order (buckets longest first) from
+// its tiles c; with `publish` also the split count and, for the host, the
+// longest bucket.  Run by one whole wave (tid < 64; c = 0 from tid 33 on).
+__device__ inline uint32_t order_bucket_start(const OrderK &o, uint32_t c, bool publish) {
+    const int tid = threadIdx.x, b = 32 - tid;
     uint32_t inc = c;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
         const uint32_t x = __shfl_up(inc, d);
         if (tid >= d) inc += x;
     }
-    if (b >= 0) {
-        uint32_t run = inc - c;
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
-            const uint32_t x = s_cnt[w * kOrderBuckets + b];
-            s_cnt[w * kOrderBuckets + b] = run;
-            run += x;
-        }
-    }
+    if (!publish) return inc - c;   // block-uniform
     // the tiles the blend splits, a prefix of the order: those of the
     // buckets from the lowest one >= split_bucket that leaves at most
     // max_split tiles in it and above (whole buckets)
@@ -112,62 +92,74 @@ __device__ inline void order_bucket_starts(const OrderK &o, uint32_t *s_cnt) {
     if (o.max_bucket && tid == 0)
         __hip_atomic_store(o.max_bucket, nz ? (uint32_t)(32 - (__ffsll((long long)nz) - 1)) : 0u,
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    return inc - c;
 }
 
-// One block of NT threads orders the tiles (s_cnt: order_lds_words(NT)
-// words of LDS).  The tiles are counted per bucket; the counters then
-// become the starts in every bucket, and every tile goes to its start plus
-// its rank.  PER_WAVE: each wave counts on counters of its own (within a
-// bucket the tiles keep the input's order: wave, item, lane); else all
-// waves share one set (fewer registers; within a bucket the order depends
-// on the timing of the waves).
-template <int NT, bool PER_WAVE>
-__device__ void order_tiles_block(const OrderK &o, uint32_t *s_cnt) {
+// Share `share` of n_shares blocks of NT threads that order the n tiles
+// tile_at(0 .. n - 1) by bucket_of(tile) into o.tile_out (s_cnt:
+// order_lds_words(NT) words of LDS).  Every block counts all tiles (a few
+// loads and LDS adds per thread, on two copies of the counters per wave) and
+// places those of its share only: after the tiles of longer buckets and
+// after those of the same bucket in the shares before it.  No block waits for
+// another.
+template <int NT, typename Tile, typename Bucket>
+__device__ void order_tiles_share(const OrderK &o, int n, int share, int n_shares, uint32_t *s_cnt,
+                                  Tile tile_at, Bucket bucket_of) {
     constexpr int kPer = 8;   // tiles per thread and round: all loads of a round in flight
-    constexpr int kWaves = PER_WAVE ? NT / 64 : 1;
-    const int tid = threadIdx.x, wave = tid >> 6;
-    const int n = o.n_dev ? (int)*o.n_dev : o.n_host;
-    uint32_t *wc = s_cnt + (PER_WAVE ? wave : 0) * kOrderBuckets;
-    for (int k = tid; k < kWaves * kOrderBuckets; k += NT) s_cnt[k] = 0u;
+    constexpr int kWaves = NT / 64;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // counters: [wave, copy][bucket] of the shares before, then of the others
+    uint32_t *before = s_cnt, *after = s_cnt + 2 * kWaves * kOrderBuckets;
+    for (int k = tid; k < order_lds_words(NT); k += NT) s_cnt[k] = 0u;
     __syncthreads();
-    int t[kPer];
-    uint32_t bk[kPer], rank[kPer];
-    bool act[kPer];
-    // every lane runs every round (bounds are block-uniform) so that the
-    // wave-level matching sees the whole wave
-    auto load_rank = [&](int c0) {
+    const int per = (n + n_shares - 1) / n_shares, i0 = share * per;
+    const int i1 = i0 + per < n ? i0 + per : n;
+    const int row = (2 * wave + (lane & 1)) * kOrderBuckets;
+    for (int c0 = 0; c0 < n; c0 += kPer * NT) {
+        uint32_t bk[kPer];
 #pragma unroll
         for (int k = 0; k < kPer; ++k) {
             const int i = c0 + k * NT + tid;
-            act[k] = i < n;
-            t[k] = act[k] ? (o.tile_in ? o.tile_in[i] : i) : 0;
+            bk[k] = i < n ? bucket_of(tile_at(i)) : 0u;
         }
 #pragma unroll
-        for (int k = 0; k < kPer; ++k) bk[k] = act[k] ? length_bucket(o.ranges, t[k]) : 0u;
-        wave_bucket_rank<kPer>(wc, bk, act, rank);
-    };
-    if (n <= kPer * NT) {
-        // one round: the tiles and their ranks stay in registers
-        load_rank(0);
-        __syncthreads();
-        if (tid < 64) order_bucket_starts<kWaves>(o, s_cnt);
-        __syncthreads();
+        for (int k = 0; k < kPer; ++k) {
+            const int i = c0 + k * NT + tid;
+            if (i < n) atomicAdd(&(i < i0 ? before : after)[row + bk[k]], 1u);
+        }
+    }
+    __syncthreads();
+    if (tid < 64) {
+        uint32_t cb = 0, ca = 0;
+        if (tid <= 32) {
+#pragma unroll
+            for (int w = 0; w < 2 * kWaves; ++w) {
+                cb += before[w * kOrderBuckets + 32 - tid];
+                ca += after[w * kOrderBuckets + 32 - tid];
+            }
+        }
+        const uint32_t start = order_bucket_start(o, cb + ca, share == 0);
+        if (tid <= 32) before[32 - tid] = start + cb;
+    }
+    __syncthreads();
+    // the block's own tiles, from the running starts (shared by its waves:
+    // the order within a bucket follows their timing)
+    for (int c0 = i0; c0 < i1; c0 += kPer * NT) {
+        int t[kPer];
+        uint32_t bk[kPer], rank[kPer];
+        bool act[kPer];
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const int i = c0 + k * NT + tid;
+            act[k] = i < i1;
+            t[k] = act[k] ? tile_at(i) : 0;
+        }
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) bk[k] = act[k] ? bucket_of(t[k]) : 0u;
+        wave_bucket_rank<kPer>(before, bk, act, rank);
 #pragma unroll
         for (int k = 0; k < kPer; ++k)
-            if (act[k]) o.tile_out[wc[bk[k]] + rank[k]] = t[k];
-    } else {
-        // several rounds: counted, then loaded and ranked again from the
-        // wave's starts
-        for (int c0 = 0; c0 < n; c0 += kPer * NT) load_rank(c0);
-        __syncthreads();
-        if (tid < 64) order_bucket_starts<kWaves>(o, s_cnt);
-        __syncthreads();
-        for (int c0 = 0; c0 < n; c0 += kPer * NT) {
-            load_rank(c0);
-#pragma unroll
-            for (int k = 0; k < kPer; ++k)
-                if (act[k]) o.tile_out[rank[k]] = t[k];
-        }
+            if (act[k]) o.tile_out[rank[k]] = t[k];
     }
 }
 

@@ -8,6 +8,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 #include <string>
@@ -82,26 +83,29 @@ struct DevBuf {
     T *as() const { return static_cast<T *>(p); }
 };
 
+constexpr uint32_t kUnknownKeys = 0xffffffffu;
+
 // Per-frame scratch of one render path (a scene's tgs_render_full, or a state).
 struct Workspace {
     DevBuf g, rect, status, count, partial;
     DevBuf dkey, didx, dkey_alt, didx_alt, offs;
-    DevBuf tkey, tval, tkey_alt, tval_alt, sort, kfirst;
-    DevBuf ranges, sel, sel_list, sel_cols, rowpre, cnt, tile_order;
+    DevBuf tkey, tval, tkey_alt, tval_alt, sort, segments, kfirst;
+    DevBuf ranges, tile_len, sel, sel_list, sel_cols, rowpre, cnt, tile_order;
     HostCounters *host_cnt = nullptr;     // coherent pinned memory, written by the device
     HostCounters *host_cnt_dev = nullptr; // its device-side address
     // pinned: longest tile list's log2 bucket of some recent frame, [0] of
     // frames that render every tile, [1] of selective-rendering frames
     uint32_t *host_maxb = nullptr;
     uint32_t *host_maxb_dev = nullptr;
+    bool general = false;                 // keys as (tile id, index) words whatever the plan says
     bool frame_seg = false;               // this frame orders tiles by the per-tile sort
     uint32_t seq = 0;                     // tag of the last frame's counters
     int n = -1, W = 0, H = 0;
     size_t key_cap = 0;
     // last frame, for tgs_debug_dump
     uint32_t last_K = 0;
-    uint32_t recent_K[2] = {0xffffffffu, 0xffffffffu};   // keys of the last frame per kind
-                                                        // ([1]: selective rendering)
+    uint32_t recent_K[2] = {kUnknownKeys, kUnknownKeys};   // keys of the last frame per kind
+                                                          // ([1]: selective rendering)
     const uint32_t *last_keys = nullptr, *last_vals = nullptr;
     bool has_frame = false;
 
@@ -144,6 +148,7 @@ struct Workspace {
         if (W_ != W || H_ != H) {
             const size_t nt = (size_t)TX * TY;
             TGS_TRY(ranges.ensure(nt * sizeof(uint2)));
+            TGS_TRY(tile_len.ensure(nt * sizeof(uint32_t)));
             TGS_TRY(sel.ensure(nt));
             TGS_TRY(sel_list.ensure(nt * sizeof(int)));
             TGS_TRY(tile_order.ensure(nt * sizeof(int)));
@@ -159,19 +164,22 @@ struct Workspace {
     // Key buffers and sort scratch for at least `want` keys (capped at the
     // key limit).  Called before a frame is enqueued, or after an overflowed
     // frame has drained: the stream holds no work that uses them.
-    tgs_status ensure_keys(size_t want, int passes) {
+    // packed: keys as digit bytes and payloads (TileSortPlan); else tile ids
+    // in words, twice.
+    tgs_status ensure_keys(size_t want, bool packed) {
         if (want > (size_t)kMaxKeys) want = kMaxKeys;
-        if (want > key_cap || !tkey.p) {
-            const size_t cap = want;
-            TGS_TRY(tkey.ensure(cap * sizeof(uint32_t)));
-            TGS_TRY(tval.ensure(cap * sizeof(uint32_t)));
-            TGS_TRY(tkey_alt.ensure(cap * sizeof(uint32_t)));
-            TGS_TRY(tval_alt.ensure(cap * sizeof(uint32_t)));
-            TGS_TRY(kfirst.ensure(key_blocks(cap) * sizeof(uint32_t)));
-            key_cap = cap;
-        }
+        if (want < key_cap) want = key_cap;
+        // (a buffer that is large enough stays as it is)
+        TGS_TRY(tkey.ensure(packed ? want + 16 : want * sizeof(uint32_t)));
+        TGS_TRY(tval.ensure(want * sizeof(uint32_t)));
+        if (!packed) TGS_TRY(tkey_alt.ensure(want * sizeof(uint32_t)));
+        TGS_TRY(tval_alt.ensure(want * sizeof(uint32_t)));
+        TGS_TRY(kfirst.ensure(key_blocks(want) * sizeof(uint32_t)));
+        if (packed) TGS_TRY(segments.ensure(tile_sort_segment_words((uint32_t)want) * sizeof(uint32_t)));
+        key_cap = want;
         const size_t nn = (size_t)(n > 0 ? n : 1);
-        const size_t words = sort_scratch_words((uint32_t)key_cap);
+        const size_t words = packed ? tile_sort_scratch_words((uint32_t)key_cap)
+                                    : sort_scratch_words((uint32_t)key_cap);
         const size_t words_depth = sort_scratch_words((uint32_t)nn);
         TGS_TRY(sort.ensure((words > words_depth ? words : words_depth) * sizeof(uint32_t)));
         return TGS_OK;
@@ -497,10 +505,10 @@ tgs_status step_wait_counters(Workspace &ws, hipStream_t st, FrameResult &fr, bo
 }
 
 // After an overflow: let the frame drain, then grow the key buffers.
-tgs_status grow_after_overflow(Workspace &ws, const FrameResult &fr, int passes, hipStream_t st) {
+tgs_status grow_after_overflow(Workspace &ws, const FrameResult &fr, bool packed, hipStream_t st) {
     TGS_HIP(hipStreamSynchronize(st));
     const size_t want = (size_t)fr.K + fr.K / 4 + 65536;
-    return ws.ensure_keys(want, passes);
+    return ws.ensure_keys(want, packed);
 }
 
 // Key bits of a tile id on a TX x TY grid.
@@ -510,8 +518,6 @@ int tile_id_bits(int TX, int TY) {
     return bits;
 }
 
-int tile_sort_passes(int TX, int TY) { return sort_passes_for_bits(tile_id_bits(TX, TY)); }
-
 // Emit the keys in depth order, sort them by tile (stable), find tile ranges;
 // returns the per-tile lists of Gaussian indices.
 tgs_status step_keys(const tgs_scene *sc, Workspace &ws, int TX, int TY, const uint32_t *rowpre,
@@ -520,35 +526,25 @@ tgs_status step_keys(const tgs_scene *sc, Workspace &ws, int TX, int TY, const u
     const int n = sc->n;
     const uint32_t cap = (uint32_t)ws.key_cap;
     Counters *cnt = ws.cnt.as<Counters>();
-    const int bits = tile_id_bits(TX, TY);
-    const uint32_t hint = ws.recent_K[rowpre ? 1 : 0];
-    // the emission counts the tile sort's first digit per block of keys
-    // (where the sort's partitions are whole blocks), in place of that
-    // pass's counting launch
-    const bool counted = sort_takes_rows(cap, hint, 0, bits);
+    // expected keys: those of the last frame of the kind, else (a first frame,
+    // an allocation-free call) the first guess of the key capacity
+    uint32_t hint = ws.recent_K[rowpre ? 1 : 0];
+    if (hint == kUnknownKeys) hint = (uint32_t)std::min<size_t>(cap, 4 * (size_t)n + 65536);
+    TileSortPlan tp = tile_sort_plan(n, tile_id_bits(TX, TY));
+    if (ws.general) tp.packed = false;
+    // the emission counts the packed sort's first digit per block of keys
+    // where that sort's partitions are those blocks (its column scan over
+    // five rows per partition of larger sorts cost more than the counting
+    // launch: 5.0M keys 4.8 -> 8.5 us against 5.3 us)
+    const bool counted = tp.packed && tile_sort_small(cap, hint);
     {
         ProfScope ps(TGS_PROF_DUPLICATE, st);
         launch_duplicate(n, cap, cnt, didx, ws.offs.as<uint32_t>(), ws.kfirst.as<uint32_t>(),
-                         ws.rect.as<ushort4>(), rowpre, sel_cols, TX, TX * TY,
+                         ws.rect.as<ushort4>(), rowpre, sel_cols, TX, TX * TY, tp,
                          ws.tkey.as<uint32_t>(), ws.tval.as<uint32_t>(), ws.ranges.as<uint2>(),
-                         sort_count_rows(ws.sort.as<uint32_t>()),
-                         counted ? sort_first_digit_bits(bits) : 0, st);
+                         ws.tile_len.as<uint32_t>(),
+                         counted ? sort_count_rows(ws.sort.as<uint32_t>()) : nullptr, st);
         TGS_LAUNCHED("duplicate");
-    }
-    int alt = 0;
-    {
-        ProfScope ps(TGS_PROF_SORT, st);
-        alt = launch_sort_u32(&cnt->n_sorted, cap, hint, 0, bits, ws.tkey.as<uint32_t>(),
-                              ws.tval.as<uint32_t>(), ws.tkey_alt.as<uint32_t>(),
-                              ws.tval_alt.as<uint32_t>(), ws.sort.as<uint32_t>(), counted, st);
-        TGS_LAUNCHED("tile sort");
-    }
-    const uint32_t *skeys = alt ? ws.tkey_alt.as<uint32_t>() : ws.tkey.as<uint32_t>();
-    uint32_t *svals = alt ? ws.tval_alt.as<uint32_t>() : ws.tval.as<uint32_t>();
-    {
-        ProfScope ps(TGS_PROF_RANGES, st);
-        launch_ranges(cap, cnt, skeys, ws.ranges.as<uint2>(), st);
-        TGS_LAUNCHED("ranges");
     }
     // blend order: the selected tiles, or all of them, longest lists first
     OrderK order{};
@@ -562,27 +558,46 @@ tgs_status step_keys(const tgs_scene *sc, Workspace &ws, int TX, int TY, const u
     order.split_bucket = sc->split_bucket;
     order.max_split = sc->split_max;
     order.n_keys = sc->split_auto ? &cnt->n_sorted : nullptr;
+    int alt = 0;
+    if (tp.packed) {
+        ProfScope ps(TGS_PROF_SORT, st);
+        alt = launch_tile_sort(tp, cap, hint, &cnt->n_sorted, ws.tkey.as<uint8_t>(),
+                               ws.tval.as<uint32_t>(), ws.tval_alt.as<uint32_t>(),
+                               ws.sort.as<uint32_t>(), ws.segments.as<uint32_t>(), counted,
+                               ws.ranges.as<uint2>(), ws.tile_len.as<uint32_t>(), TX * TY, order, st);
+        if (order_apart(hint)) launch_order_tiles(order, st);
+        TGS_LAUNCHED("tile sort, ranges and tile order");
+        ws.last_keys = nullptr;   // the sorted ids are the tile ranges'
+    } else {
+        {
+            ProfScope ps(TGS_PROF_SORT, st);
+            alt = launch_sort_u32(&cnt->n_sorted, cap, hint, 0, tp.bits, ws.tkey.as<uint32_t>(),
+                                  ws.tval.as<uint32_t>(), ws.tkey_alt.as<uint32_t>(),
+                                  ws.tval_alt.as<uint32_t>(), ws.sort.as<uint32_t>(), st);
+            TGS_LAUNCHED("tile sort");
+        }
+        ws.last_keys = alt ? ws.tkey_alt.as<uint32_t>() : ws.tkey.as<uint32_t>();
+        ProfScope ps(TGS_PROF_RANGES, st);
+        launch_ranges(cap, cnt, ws.last_keys, ws.ranges.as<uint2>(), st);
+        launch_order_tiles(order, st);
+        TGS_LAUNCHED("ranges and tile order");
+    }
+    uint32_t *svals = alt ? ws.tval_alt.as<uint32_t>() : ws.tval.as<uint32_t>();
     if (ws.frame_seg) {
         // each tile's list, emitted in index order, by (depth bits, index)
         ProfScope ps(TGS_PROF_SORT, st);
         // lists above 2048 entries get a launch of their own when a recent
         // frame of the same kind had any (the longest list's bucket, from the
         // host copy)
-        // the blend order (below) is computed by one more block of this launch
         const uint32_t maxb = ws.host_maxb
             ? reinterpret_cast<volatile uint32_t *>(ws.host_maxb)[rowpre ? 1 : 0] : 0xffffffffu;
         launch_segment_sort(TX * TY, ws.ranges.as<uint2>(), svals,
                             alt ? ws.tval.as<uint32_t>() : ws.tval_alt.as<uint32_t>(),
-                            ws.dkey.as<uint32_t>(), maxb >= (uint32_t)kSegLongBucket, &order, st);
-        TGS_LAUNCHED("per-tile sort and tile order");
-    } else {
-        ProfScope ps(TGS_PROF_RANGES, st);
-        launch_order_tiles(order, st);
-        TGS_LAUNCHED("tile order");
+                            ws.dkey.as<uint32_t>(), maxb >= (uint32_t)kSegLongBucket, st);
+        TGS_LAUNCHED("per-tile sort");
     }
-    *sorted_vals = alt ? ws.tval_alt.as<uint32_t>() : ws.tval.as<uint32_t>();
-    ws.last_keys = skeys;
-    ws.last_vals = *sorted_vals;
+    *sorted_vals = svals;
+    ws.last_vals = svals;
     ws.has_frame = true;
     return TGS_OK;
 }
@@ -862,8 +877,8 @@ tgs_status tgs_render_full(tgs_scene *sc, const tgs_camera *cam, tgs_frame_out *
     Workspace &ws = sc->ws;
     TGS_TRY(ws.prepare(sc->n, W, H));
     const CamK ck = make_camk(cam);
-    const int passes = tile_sort_passes(TX, TY);
-    TGS_TRY(ws.ensure_keys(ws.key_cap ? ws.key_cap : 4 * (size_t)sc->n + 65536, passes));
+    const bool packed = tile_sort_plan(sc->n, tile_id_bits(TX, TY)).packed;
+    TGS_TRY(ws.ensure_keys(ws.key_cap ? ws.key_cap : 4 * (size_t)sc->n + 65536, packed));
     FrameResult fr;
     for (;;) {
         TGS_TRY(step_preprocess(sc, ws, ck, no_cull(0.2f, ws), st));
@@ -891,7 +906,7 @@ tgs_status tgs_render_full(tgs_scene *sc, const tgs_camera *cam, tgs_frame_out *
         TGS_TRY(step_wait_counters(ws, st, fr, &overflow));
         ws.recent_K[0] = fr.K;
         if (!overflow) break;
-        TGS_TRY(grow_after_overflow(ws, fr, passes, st));
+        TGS_TRY(grow_after_overflow(ws, fr, packed, st));
     }
     sc->last_W = W;
     sc->last_H = H;
@@ -961,13 +976,16 @@ struct Carve {
 };
 
 // Lays the workspace of a full render (n Gaussians, W x H, key_cap keys) over
-// [base, base + cap); false if it does not fit.
-bool layout_full(Workspace &ws, char *base, size_t cap, int n, int W, int H, size_t key_cap) {
+// [base, base + cap), with packed keys or with (tile id, index) words; false
+// if it does not fit.  The words' layout sets the capacity of a size; packed
+// keys take less of the array, except for the count rows of very few keys.
+bool layout_full(Workspace &ws, char *base, size_t cap, int n, int W, int H, size_t key_cap, bool packed) {
     Carve c{base, cap, 0};
     const size_t nn = (size_t)(n > 0 ? n : 1);
     const int TX = (W + 15) / 16, TY = (H + 15) / 16;
     const size_t nt = (size_t)TX * TY;
-    const size_t sort_words = std::max(sort_scratch_words((uint32_t)key_cap),
+    const size_t sort_words = std::max(packed ? tile_sort_scratch_words((uint32_t)key_cap)
+                                              : sort_scratch_words((uint32_t)key_cap),
                                        sort_scratch_words((uint32_t)nn));
     bool ok = c.take(ws.g, nn * 4 * sizeof(float4)) && c.take(ws.rect, nn * sizeof(ushort4)) &&
               c.take(ws.status, nn) && c.take(ws.count, (nn + 4) * sizeof(uint32_t)) &&
@@ -979,8 +997,11 @@ bool layout_full(Workspace &ws, char *base, size_t cap, int n, int W, int H, siz
               c.take(ws.sel_cols, nt * sizeof(int)) &&
               c.take(ws.rowpre, (size_t)TY * (TX + 1) * sizeof(uint32_t)) &&
               c.take(ws.cnt, sizeof(Counters)) && c.take(ws.sort, sort_words * sizeof(uint32_t)) &&
-              c.take(ws.tkey, key_cap * 4) && c.take(ws.tval, key_cap * 4) &&
-              c.take(ws.tkey_alt, key_cap * 4) && c.take(ws.tval_alt, key_cap * 4) &&
+              c.take(ws.tkey, packed ? key_cap + 16 : key_cap * 4) && c.take(ws.tval, key_cap * 4) &&
+              (packed ? c.take(ws.segments, tile_sort_segment_words((uint32_t)key_cap) * 4) &&
+                            c.take(ws.tile_len, nt * 4)
+                      : c.take(ws.tkey_alt, key_cap * 4)) &&
+              c.take(ws.tval_alt, key_cap * 4) &&
               c.take(ws.kfirst, key_blocks(key_cap) * sizeof(uint32_t));
     void *hc = ok ? c.raw(sizeof(HostCounters)) : nullptr;
     void *mb = hc ? c.raw(2 * sizeof(uint32_t)) : nullptr;
@@ -995,6 +1016,7 @@ bool layout_full(Workspace &ws, char *base, size_t cap, int n, int W, int H, siz
     ws.W = W;
     ws.H = H;
     ws.key_cap = key_cap;
+    ws.general = !packed;
     return true;
 }
 
@@ -1016,7 +1038,7 @@ tgs_status tgs_render_full_noalloc(const tgs_scene *sc, const tgs_camera *cam, t
     size_t lo = 0, hi = kNoAllocBytes / 16;
     {
         Workspace probe;
-        if (!layout_full(probe, base, kNoAllocBytes, sc->n, W, H, kKeyBlock))
+        if (!layout_full(probe, base, kNoAllocBytes, sc->n, W, H, kKeyBlock, false))
             return fail(TGS_ERR_CAPACITY, std::to_string(sc->n) + " Gaussians at " + std::to_string(W) +
                                               "x" + std::to_string(H) + " do not fit the " +
                                               std::to_string(kNoAllocBytes >> 20) +
@@ -1026,10 +1048,12 @@ tgs_status tgs_render_full_noalloc(const tgs_scene *sc, const tgs_camera *cam, t
     while (lo < hi) {
         const size_t mid = lo + (hi - lo + 1) / 2;
         Workspace probe;
-        if (layout_full(probe, base, kNoAllocBytes, sc->n, W, H, mid)) lo = mid;
+        if (layout_full(probe, base, kNoAllocBytes, sc->n, W, H, mid, false)) lo = mid;
         else hi = mid - 1;
     }
-    if (!layout_full(ws, base, kNoAllocBytes, sc->n, W, H, lo))
+    const bool packed = tile_sort_plan(sc->n, tile_id_bits(TX, TY)).packed;
+    if (!(packed && layout_full(ws, base, kNoAllocBytes, sc->n, W, H, lo, true)) &&
+        !layout_full(ws, base, kNoAllocBytes, sc->n, W, H, lo, false))
         return fail(TGS_ERR_DEVICE, "scratch layout failed");
     // no profiling events in this call (creating one allocates)
     struct NoAllocScope {
@@ -1150,8 +1174,8 @@ tgs_status tgs_render_temporal(tgs_state *s, const tgs_camera *cam, tgs_frame_ou
     else
         kind = TGS_FRAME_TGS;
 
-    const int passes = tile_sort_passes(TX, TY);
-    TGS_TRY(ws.ensure_keys(ws.key_cap ? ws.key_cap : 4 * (size_t)sc->n + 65536, passes));
+    const bool packed = tile_sort_plan(sc->n, tile_id_bits(TX, TY)).packed;
+    TGS_TRY(ws.ensure_keys(ws.key_cap ? ws.key_cap : 4 * (size_t)sc->n + 65536, packed));
     FrameResult fr;
     for (;;) {
         const uint32_t *vals = nullptr;
@@ -1312,7 +1336,7 @@ tgs_status tgs_render_temporal(tgs_state *s, const tgs_camera *cam, tgs_frame_ou
         TGS_TRY(step_wait_counters(ws, st, fr, &overflow));
         ws.recent_K[kind == TGS_FRAME_TGS ? 1 : 0] = fr.K;
         if (!overflow) break;
-        TGS_TRY(grow_after_overflow(ws, fr, passes, st));
+        TGS_TRY(grow_after_overflow(ws, fr, packed, st));
     }
     if (kind != TGS_FRAME_TGS) {
         memcpy(s->ref_w2c, cam->world_to_cam, sizeof(s->ref_w2c));
@@ -1430,6 +1454,37 @@ tgs_status tgs_state_import(tgs_state *s, const void *host, size_t nbytes) {
     return TGS_OK;
 }
 
+}  // extern "C"
+
+namespace {
+
+// Tile ids [first, first + count) of the last frame's sorted keys (nt tiles;
+// the device is idle).  The packed tile sort leaves no sorted ids: they are
+// those of the tile ranges.
+tgs_status dump_sorted_keys(const Workspace &ws, size_t nt, size_t first, size_t count, uint32_t *dst) {
+    if (count == 0) return TGS_OK;
+    if (ws.last_keys) {
+        TGS_HIP(hipMemcpy(dst, ws.last_keys + first, count * sizeof(uint32_t), hipMemcpyDeviceToHost));
+        return TGS_OK;
+    }
+    std::vector<uint2> r;
+    try {
+        r.resize(nt);
+    } catch (...) {
+        return fail(TGS_ERR_OUT_OF_MEMORY, "host allocation failed");
+    }
+    TGS_HIP(hipMemcpy(r.data(), ws.ranges.p, nt * sizeof(uint2), hipMemcpyDeviceToHost));
+    for (size_t t = 0; t < nt; ++t) {
+        const size_t a = std::max((size_t)r[t].x, first), b = std::min((size_t)r[t].y, first + count);
+        for (size_t k = a; k < b; ++k) dst[k - first] = (uint32_t)t;
+    }
+    return TGS_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
 tgs_status tgs_debug_dump(const tgs_scene *scene, const tgs_state *state, int32_t what, void *host,
                           size_t *nbytes) {
     g_err.clear();
@@ -1445,7 +1500,7 @@ tgs_status tgs_debug_dump(const tgs_scene *scene, const tgs_state *state, int32_
     if (!ws.has_frame) return fail(TGS_ERR_INVALID_ARG, "no frame has been rendered yet");
     switch (what) {
         case TGS_DUMP_SORTED_VALUES: src = ws.last_vals; size = (size_t)ws.last_K * 4; break;
-        case TGS_DUMP_SORTED_KEYS: src = ws.last_keys; size = (size_t)ws.last_K * 4; break;
+        case TGS_DUMP_SORTED_KEYS: size = (size_t)ws.last_K * 4; break;
         case TGS_DUMP_TILE_RANGES: src = ws.ranges.p; size = nt * 8; break;
         case TGS_DUMP_RECTS: src = ws.rect.p; size = (size_t)n * 8; break;
         case TGS_DUMP_STATUS: src = ws.status.p; size = (size_t)n; break;
@@ -1479,6 +1534,8 @@ tgs_status tgs_debug_dump(const tgs_scene *scene, const tgs_state *state, int32_
             dst[(size_t)i * 12 + 7] = 0.0f;
             dst[(size_t)i * 12 + 11] = 0.0f;
         }
+    } else if (what == TGS_DUMP_SORTED_KEYS) {
+        TGS_TRY(dump_sorted_keys(ws, nt, 0, ws.last_K, static_cast<uint32_t *>(host)));
     } else if (size) {
         TGS_HIP(hipMemcpy(host, src, size, hipMemcpyDeviceToHost));
     }
@@ -1498,9 +1555,13 @@ tgs_status tgs_debug_dump_range(const tgs_scene *scene, const tgs_state *state, 
     if (first > (size_t)ws.last_K || count > (size_t)ws.last_K - first)
         return fail(TGS_ERR_INVALID_ARG, "range past the frame's keys");
     if (count == 0) return TGS_OK;
-    const uint32_t *src = what == TGS_DUMP_SORTED_VALUES ? ws.last_vals : ws.last_keys;
     TGS_HIP(hipDeviceSynchronize());
-    TGS_HIP(hipMemcpy(host, src + first, count * sizeof(uint32_t), hipMemcpyDeviceToHost));
+    if (what == TGS_DUMP_SORTED_KEYS) {
+        const int W = state ? state->W : scene->last_W, H = state ? state->H : scene->last_H;
+        return dump_sorted_keys(ws, (size_t)((W + 15) / 16) * ((H + 15) / 16), first, count,
+                                static_cast<uint32_t *>(host));
+    }
+    TGS_HIP(hipMemcpy(host, ws.last_vals + first, count * sizeof(uint32_t), hipMemcpyDeviceToHost));
     return TGS_OK;
 }
 

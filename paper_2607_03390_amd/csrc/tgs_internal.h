@@ -173,16 +173,18 @@ __device__ inline void mark_key_blocks(uint32_t *kfirst, uint32_t nb, uint32_t s
 // ---- launchers (k_keys.hip) ----
 // Emits the cnt->n_sorted keys of the cnt->n_visible depth-ordered Gaussians
 // (cap bounds n_sorted for the grid; nothing is emitted past the key
-// capacity) and clears the tile ranges (filled by launch_ranges after the
-// tile sort).  rowpre / sel_cols are NULL in frames that render every tile.
-// rows (optional): per block of kKeyBlock keys, the counts of the tile
-// sort's first digit (key bits [0, row_bits)) in row b of rows[b][256] (see
-// launch_sort_u32).
+// capacity) and clears the tile ranges and lengths (filled by the tile sort, or
+// the ranges by launch_ranges after it).  rowpre / sel_cols are NULL in frames that render every tile.
+// Keys: tile id to tkey and index to tval, or (tp.packed) the low digit bytes
+// to tkey and the payload to tval (launch_tile_sort).  rows (optional): per
+// block of kKeyBlock keys, the counts of the low digit in row b of
+// rows[b][256].
+struct TileSortPlan;
 void launch_duplicate(int n, uint32_t cap, const Counters *cnt, const uint32_t *didx,
                       const uint32_t *offs, const uint32_t *kfirst, const ushort4 *rect,
                       const uint32_t *rowpre, const int *sel_cols, int TX, int n_tiles,
-                      uint32_t *tkey, uint32_t *tval, uint2 *ranges, uint32_t *rows,
-                      int row_bits, hipStream_t st);
+                      const TileSortPlan &tp, uint32_t *tkey, uint32_t *tval, uint2 *ranges,
+                      uint32_t *tile_len, uint32_t *rows, hipStream_t st);
 // Ranges of the cnt->n_sorted tile-sorted keys; cap bounds n_sorted for the grid.
 void launch_ranges(uint32_t cap, const Counters *cnt, const uint32_t *keys, uint2 *ranges,
                    hipStream_t st);
@@ -209,6 +211,8 @@ struct OrderK {
     int max_split;
     const uint32_t *n_keys;
 };
+// (kOrderShares blocks, each placing its share of the tiles.)
+constexpr int kOrderShares = 8;
 void launch_order_tiles(const OrderK &o, hipStream_t st);
 
 // ---- launchers (k_sort.hip) ----
@@ -221,17 +225,50 @@ size_t sort_scratch_words(uint32_t max_keys);
 // (n_max bounds it), else n_max.  Returns 1 if the result is in the alt buffers.
 // n_hint: the expected key count (e.g. a recent frame's); it picks the
 // partition size (small partitions fill the chip for small sorts).
-// counted: the first pass's digit counts of every kKeyBlock keys are
-// already in sort_count_rows(scratch) (written by the key emission), so that
-// pass has no counting launch; allowed only where sort_takes_rows says so.
 int launch_sort_u32(const uint32_t *n_dev, uint32_t n_max, uint32_t n_hint, int begin_bit,
                     int bits, uint32_t *keys, uint32_t *vals, uint32_t *keys_alt,
-                    uint32_t *vals_alt, uint32_t *scratch, bool counted, hipStream_t st);
-// Whether launch_sort_u32 with these sizes can take counted rows, and the
-// width of its first digit; where the rows go in its scratch.
-bool sort_takes_rows(uint32_t n_max, uint32_t n_hint, int begin_bit, int bits);
-int sort_first_digit_bits(int bits);
+                    uint32_t *vals_alt, uint32_t *scratch, hipStream_t st);
+// The sorts' scratch: chunk sums, then count rows of 256 digits.
 uint32_t *sort_count_rows(uint32_t *scratch);
+// Column scan of the count rows of ceil(n / tile) partitions (n = *n_dev or
+// n_host): offsets within the chunk in place, the chunks' digit sums to sums.
+void launch_colscan(const uint32_t *n_dev, uint32_t n_host, uint32_t tile, uint32_t np, int tables,
+                    uint32_t *table, uint32_t *sums, hipStream_t st);
+// ---- launchers (k_tilesort.hip) ----
+// How the keys of a scene of n Gaussians on a grid of tile ids of `bits` bits
+// are laid out and sorted: packed (grids of up to 2^16 tiles whose high
+// digit fits beside the index), or as (tile id, index) word pairs by
+// launch_sort_u32.
+struct TileSortPlan {
+    int bits;         // of a tile id
+    int index_bits;   // of a Gaussian index
+    int lo, hi;       // packed: widths of the two digits (hi = 0: one pass)
+    bool packed;
+};
+TileSortPlan tile_sort_plan(int n, int bits);
+// Whether the sort takes partitions of kKeyBlock keys (n_hint: the expected
+// key count, e.g. a recent frame's): the emission may then count the low
+// digits of its blocks of keys into sort_count_rows(scratch).
+bool tile_sort_small(uint32_t cap, uint32_t n_hint);
+// Stable sort of the *n_dev (<= cap) payloads (high digit << index_bits |
+// index) by (high digit, low digit dig), to Gaussian indices; the tile
+// ranges (of the tiles with keys; the others stay as the emission cleared
+// them) and, unless order_apart(n_hint), the blend order of the tiles (order).
+// counted: the emission has counted.  scratch and segments:
+// tile_sort_scratch_words(cap) and tile_sort_segment_words(cap) words;
+// tile_len: n_tiles words, cleared by the emission.  Returns 1 if the result is in pay_alt, 0 if in pay.
+// Sorts of more keys than this leave the order to a launch of its own: a
+// tile's length is summed by one add per partition of its low digit, hundreds
+// of them to one address (2.27G keys: 1.7 -> 3.9 ms for the counting launch,
+// 5.0M keys: 6.4 -> 8.8 us, against a launch of 10 us).
+inline bool order_apart(uint32_t n_hint) { return n_hint > (32u << 20); }
+size_t tile_sort_scratch_words(uint32_t max_keys);
+size_t tile_sort_segment_words(uint32_t max_keys);
+int launch_tile_sort(const TileSortPlan &tp, uint32_t cap, uint32_t n_hint, const uint32_t *n_dev,
+                     const uint8_t *dig, uint32_t *pay, uint32_t *pay_alt, uint32_t *scratch,
+                     uint32_t *segments, bool counted, uint2 *ranges, uint32_t *tile_len, int n_tiles,
+                     const OrderK &order, hipStream_t st);
+
 // Depth order of the Gaussians with count[i] > 0 among i < n, stable by index
 // (keys dkey[i], the depth's float bits): four passes (dkey -> a -> b -> a ->
 // v_b; k_b may alias dkey).  With rowpre (a selective-rendering frame) the
@@ -261,11 +298,8 @@ void launch_count_scan(int n, uint32_t *count, const ushort4 *rect, const uint32
                        HostCounters *host, uint32_t tag, hipStream_t st);
 // long_lists: lists above 2048 entries are expected (a launch of their own
 // for them); otherwise the few there are take a slower in-block path.
-// order (optional): the blend order of the tiles is computed by one more
-// block of the short-list launch, beside the sorting blocks.
 void launch_segment_sort(int n_tiles, const uint2 *ranges, uint32_t *vals, uint32_t *tmp,
-                         const uint32_t *dkey, bool long_lists, const OrderK *order,
-                         hipStream_t st);
+                         const uint32_t *dkey, bool long_lists, hipStream_t st);
 // Length bucket (floor(log2 len) + 1) from which a recent frame's lists make
 // the long-list launch worth its cost: lists of 2048 entries and more.
 constexpr int kSegLongBucket = 12;

@@ -277,6 +277,20 @@ def test_full_parity_large_grids(W, H, log_scale):
     _full_parity(sc, [cam], sample_tiles=sample, label=f"grid {TX}x{TY}")
 
 
+# one tile; the last grid of one pass and the first of two; the last grid of
+# the packed keys (65536 tiles: digits of 8 and 8 bits), one row past it
+@pytest.mark.parametrize("W,H,n", [(16, 16, 900), (256, 256, 6000), (257, 256, 6000), (33, 600, 5000),
+                                   (4096, 4096, 3000), (4096, 4112, 3000)])
+def test_tile_sort_grid_edges(W, H, n):
+    """Tile sorts at the edges of their digit widths: lists, ranges and sorted
+    ids bit-exact, over several frames of one scene."""
+    sc = synth.small_scene(n, 17, degree=0)
+    cams = [synth.make_camera(synth.look_at(e, (0, 0, 0)), W, H) for e in ((0.2, -3.0, 0.7), (9.0, 2.0, 1.0))]
+    TX, TY = cams[0].tiles
+    sample = None if TX * TY < 1000 else np.random.default_rng(2).choice(TX * TY, 40, replace=False)
+    _full_parity(sc, cams, sample_tiles=sample, label=f"tile sort {TX}x{TY}")
+
+
 def test_full_parity_object_subset():
     w = synth.workload("object", n_gaussians=40_000)
     _full_parity(w.scene, [w.cameras[0], w.cameras[37]], label="object 40k")

@@ -12,48 +12,71 @@ namespace tgs {
 
 namespace {
 
-// Tile (tx, ty) of the r-th key of a Gaussian with tile rectangle rc:
-// row-major over the rectangle, or (rowpre != NULL) over its selected tiles,
-// rows first, O(1) per row from the per-row prefix sums of the tile mask.
-__device__ inline void key_tile_xy(uint32_t r, ushort4 rc, const uint32_t *rowpre,
-                                   const int *sel_cols, int TX, int &tx, int &ty) {
-    if (!rowpre) {
-        const uint32_t w = (uint32_t)(rc.z - rc.x + 1);
-        ty = rc.y + (int)(r / w);
-        tx = rc.x + (int)(r % w);
+// Row and column of key r of a rectangle w tiles wide (r < 2^20, w <= 1024:
+// the quotient of the hardware reciprocal is off by at most one).
+__device__ inline void divide_row(uint32_t r, uint32_t w, uint32_t &row, uint32_t &col) {
+    uint32_t q = (uint32_t)((float)r * __builtin_amdgcn_rcpf((float)w));
+    int rem = (int)(r - q * w);
+    if (rem < 0) {
+        q -= 1;
+        rem += (int)w;
+    } else if (rem >= (int)w) {
+        q += 1;
+        rem -= (int)w;
+    }
+    row = q;
+    col = (uint32_t)rem;
+}
+
+// The keys of one Gaussian in order: its rectangle's tiles row by row, or
+// (sat != NULL) the selected ones among them.  seek(r) goes to its r-th key,
+// next() to the one after (the Gaussian has it).
+struct KeyWalk {
+    ushort4 rc;
+    int tx, ty;
+    int pos, end;   // sat: entries of the row's selected columns, current and last + 1
+};
+
+__device__ inline void key_seek(KeyWalk &k, uint32_t r, const uint32_t *sat, const int *sel_cols, int TX) {
+    const ushort4 rc = k.rc;
+    if (!sat) {
+        uint32_t row, col;
+        divide_row(r, (uint32_t)(rc.z - rc.x + 1), row, col);
+        k.tx = (int)rc.x + (int)col;
+        k.ty = (int)rc.y + (int)row;
         return;
     }
-    // four rows per step (eight independent loads), then the row holding the
-    // r-th selected tile among them
-    ty = rc.y;
+    // the row holding the r-th selected tile, by bisection on the summed area
+    // table (needles cross hundreds of tile rows)
     const size_t s = (size_t)(TX + 1);
-    const uint32_t *row = rowpre + (size_t)ty * s;
-    for (;;) {
-        if (ty > (int)rc.w) {   // r past the Gaussian's count: cannot happen
-            tx = rc.x;
-            ty = rc.w;
-            return;
+    auto upto = [&](int y) { return sat[y * s + rc.z + 1] - sat[y * s + rc.x]; };   // in rows below y
+    const uint32_t base = upto(rc.y);
+    int lo = rc.y, hi = rc.w;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (upto(mid + 1) - base > r) hi = mid;
+        else lo = mid + 1;
+    }
+    const uint32_t *row = sat + lo * s, *below = row + s;
+    const uint32_t a0 = row[rc.x], a1 = row[rc.z + 1], b0 = below[rc.x], b1 = below[rc.z + 1];
+    k.ty = lo;
+    k.pos = (int)(b0 - a0 + (r - (a1 - a0 - base)));
+    k.end = (int)(b1 - a1);
+    k.tx = sel_cols[(size_t)lo * TX + k.pos];
+}
+
+__device__ inline void key_next(KeyWalk &k, uint32_t r, const uint32_t *sat, const int *sel_cols, int TX) {
+    if (!sat) {
+        k.tx += 1;
+        if (k.tx > (int)k.rc.z) {
+            k.tx = k.rc.x;
+            k.ty += 1;
         }
-        uint32_t c[4], b[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const bool in = ty + k <= (int)rc.w;
-            b[k] = in ? row[k * s + rc.x] : 0u;
-            c[k] = in ? row[k * s + rc.z + 1] - b[k] : 0u;
-        }
-        int k = 0;
-        while (k < 3 && r >= c[k]) {
-            r -= c[k];
-            ++k;
-        }
-        if (r < c[k]) {
-            ty += k;
-            tx = sel_cols[(size_t)ty * TX + b[k] + r];
-            return;
-        }
-        r -= c[k];
-        ty += 4;
-        row += 4 * s;
+    } else if (k.pos + 1 < k.end) {
+        k.pos += 1;
+        k.tx = sel_cols[(size_t)k.ty * TX + k.pos];
+    } else {
+        key_seek(k, r, sat, sel_cols, TX);
     }
 }
 
@@ -67,7 +90,7 @@ struct DupIo {
     const uint32_t *offs;
     const uint32_t *kfirst;
     const ushort4 *rect;
-    const uint32_t *rowpre;
+    const uint32_t *sat;
     const int *sel_cols;
     int TX;
     int n_tiles;
@@ -197,11 +220,16 @@ __global__ __launch_bounds__(256) void duplicate_kernel(DupIo io, uint32_t *tkey
         r[k] = pc - s_off[own[k]];
         rc[k] = io.rect[g[k]];
     }
+    KeyWalk walk;
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
-        int tx, ty;
-        key_tile_xy(r[k], rc[k], io.rowpre, io.sel_cols, io.TX, tx, ty);
-        key[k] = (uint32_t)(ty * io.TX + tx);
+        if (k == 0 || own[k] != own[k - 1]) {
+            walk.rc = rc[k];
+            key_seek(walk, r[k], io.sat, io.sel_cols, io.TX);
+        } else if (p + k < P1) {
+            key_next(walk, r[k], io.sat, io.sel_cols, io.TX);
+        }
+        key[k] = (uint32_t)(walk.ty * io.TX + walk.tx);
     }
     const uint32_t lmask = PACKED ? (1u << io.lo_bits) - 1u : 0u;
     uint32_t val[kPer];
@@ -292,7 +320,7 @@ __global__ __launch_bounds__(256) void order_tiles_kernel(OrderK o) {
 
 void launch_duplicate(int n, uint32_t cap, const Counters *cnt, const uint32_t *didx,
                       const uint32_t *offs, const uint32_t *kfirst, const ushort4 *rect,
-                      const uint32_t *rowpre, const int *sel_cols, int TX, int n_tiles,
+                      const uint32_t *sat, const int *sel_cols, int TX, int n_tiles,
                       const TileSortPlan &tp, uint32_t *tkey, uint32_t *tval, uint2 *ranges,
                       uint32_t *tile_len, uint32_t *rows, hipStream_t st) {
     if (n <= 0 || cap == 0) {
@@ -301,7 +329,7 @@ void launch_duplicate(int n, uint32_t cap, const Counters *cnt, const uint32_t *
         return;
     }
     const uint32_t blocks = (cap + kDupKeys - 1) / kDupKeys;
-    const DupIo io{cnt, didx, offs, kfirst, rect, rowpre, sel_cols, TX, n_tiles, ranges,
+    const DupIo io{cnt, didx, offs, kfirst, rect, sat, sel_cols, TX, n_tiles, ranges,
                    tile_len, rows, tp.lo, tp.index_bits};
     if (tp.packed) duplicate_kernel<true><<<blocks, 256, 0, st>>>(io, tkey, tval);
     else duplicate_kernel<false><<<blocks, 256, 0, st>>>(io, tkey, tval);

@@ -69,12 +69,12 @@ __device__ inline T block_exscan(T v, T *s_wave, T *total) {
 // follows index order).
 __global__ __launch_bounds__(kScanThreads) void count_partials_kernel(int n, uint32_t *count,
                                                                       const ushort4 *rect,
-                                                                      const uint32_t *rowpre, int TX,
+                                                                      const uint32_t *sat, int TX,
                                                                       uint32_t *part) {
     __shared__ uint32_t s_w[4];
     const int base = blockIdx.x * kScanBlock + threadIdx.x * kScanPer;
     uint32_t keys = 0, nz = 0;
-    if (rowpre) {
+    if (sat) {
         // the four rectangles are loaded before the first count
         ushort4 r[kScanPer];
 #pragma unroll
@@ -82,7 +82,7 @@ __global__ __launch_bounds__(kScanThreads) void count_partials_kernel(int n, uin
             r[k] = base + k < n ? rect[base + k] : make_ushort4(1, 0, 0, 0);
 #pragma unroll
         for (int k = 0; k < kScanPer; ++k) {
-            const uint32_t c = masked_count(r[k], rowpre, TX);
+            const uint32_t c = masked_count(r[k], sat, TX);
             if (base + k < n) count[base + k] = c;
             keys += c;
             nz += c ? 1u : 0u;
@@ -461,13 +461,13 @@ __global__ __launch_bounds__(kLongThreads) void segment_sort_long_kernel(const u
 
 int count_scan_blocks(int n) { return (n + kScanBlock - 1) / kScanBlock; }
 
-void launch_count_scan(int n, uint32_t *count, const ushort4 *rect, const uint32_t *rowpre, int TX,
+void launch_count_scan(int n, uint32_t *count, const ushort4 *rect, const uint32_t *sat, int TX,
                        uint32_t *part, uint32_t *vidx, uint32_t *voffs, uint32_t *kfirst,
                        Counters *cnt, uint32_t cap, const uint32_t *pre_partial, int n_pre,
                        HostCounters *host, uint32_t tag, hipStream_t st) {
     const int nb = count_scan_blocks(n > 0 ? n : 0);
     if (nb > 0)
-        count_partials_kernel<<<nb, kScanThreads, 0, st>>>(n, count, rect, rowpre, TX, part);
+        count_partials_kernel<<<nb, kScanThreads, 0, st>>>(n, count, rect, sat, TX, part);
     // at least one block: the last one publishes the counters
     count_emit_kernel<<<nb > 0 ? nb : 1, kScanThreads, 0, st>>>(n, nb, count, part, vidx, voffs,
                                                                 kfirst, pre_partial, n_pre, cnt,

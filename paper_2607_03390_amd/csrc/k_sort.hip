@@ -64,8 +64,8 @@ __device__ inline uint32_t key_count(const uint32_t *n_dev, uint32_t n_host) {
 struct DepthIo {
     uint32_t *count;            // key count per Gaussian
     const ushort4 *rect;        // first pass of a selective frame: recount from
-    const uint32_t *rowpre;     // the rectangles and the tile mask's row prefix
-    int TX;                     // sums (rowpre NULL: count is final)
+    const uint32_t *sat;        // the rectangles and the tile mask's summed area
+    int TX;                     // table (sat NULL: count is final)
     uint32_t *offs;             // last pass: start of each sorted Gaussian's keys
     uint32_t *kfirst;           // last pass: owner of each key block (key_blocks(cap))
     Counters *cnt;
@@ -126,8 +126,8 @@ __global__ __launch_bounds__(kSortThreads) void sort_upsweep_kernel(
         dg[j] = (kin[ic] >> shift) & ((1u << nbits) - 1u);
         if (MODE == kFirst) {
             uint32_t c;
-            if (io.rowpre) {
-                c = masked_count(io.rect[ic], io.rowpre, io.TX);
+            if (io.sat) {
+                c = masked_count(io.rect[ic], io.sat, io.TX);
                 if (keep[j]) io.count[idx] = c;
             } else {
                 c = io.count[ic];
@@ -619,7 +619,7 @@ int launch_sort_u32(const uint32_t *n_dev, uint32_t n_max, uint32_t n_hint, int 
     return passes & 1;
 }
 
-void launch_depth_sort(int n, uint32_t *count, const ushort4 *rect, const uint32_t *rowpre, int TX,
+void launch_depth_sort(int n, uint32_t *count, const ushort4 *rect, const uint32_t *sat, int TX,
                        const uint32_t *dkey, uint32_t *k_a, uint32_t *v_a, uint32_t *k_b,
                        uint32_t *v_b, uint32_t *offs, uint32_t *kfirst, uint32_t *scratch,
                        Counters *cnt, uint32_t cap, const uint32_t *pre_partial, int n_pre,
@@ -627,7 +627,7 @@ void launch_depth_sort(int n, uint32_t *count, const ushort4 *rect, const uint32
     DepthIo io;
     io.count = count;
     io.rect = rect;
-    io.rowpre = rowpre;
+    io.sat = sat;
     io.TX = TX;
     io.offs = offs;
     io.kfirst = kfirst;

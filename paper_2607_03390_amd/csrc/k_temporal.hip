@@ -10,7 +10,7 @@
 //    (Gaussian, tile) pair with a wave ballot over the tile's 256 pixels,
 //    the pairs of 1024 Gaussians dealt out over the four waves of a block;
 //  - tile selection and compaction in one launch, one block per tile row,
-//    including the per-row prefix sums of the mask used by the key counts.
+//    including the summed area table of the mask used by the key counts.
 // (The stitching of the tiles that are not re-rendered, Eq. 4, runs in the
 // blend launch: stitch.h.)
 // All of these are HBM- or latency-bound; none is a dense contraction.
@@ -55,28 +55,6 @@ __global__ __launch_bounds__(256) void forward_warp_kernel(WarpK w, const float 
 }
 
 __global__ __launch_bounds__(256) void fill_query_kernel(FillK f) { fill_query_tile(f, blockIdx.x); }
-
-__device__ inline uint32_t block_exclusive_scan256(uint32_t v, uint32_t *s_wave, uint32_t *total) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t inc = v;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t o = __shfl_up(inc, d);
-        if (lane >= d) inc += o;
-    }
-    if (lane == 63) s_wave[wave] = inc;
-    __syncthreads();
-    uint32_t off = 0, tot = 0;
-#pragma unroll
-    for (int x = 0; x < 4; ++x) {
-        const uint32_t c = s_wave[x];
-        if (x < wave) off += c;
-        tot += c;
-    }
-    __syncthreads();
-    *total = tot;
-    return off + inc - v;
-}
 
 // value of x in lane j (j uniform across the wave)
 __device__ inline float lane_f(float x, int j) {
@@ -223,52 +201,120 @@ __global__ __launch_bounds__(kOccThreads) void occluded_kernel(WarpK w, int n,
     }
 }
 
-// One block per tile row: selected = occluded | unmatched (or every tile),
-// the row's exclusive prefix sums rowpre[ty][0..TX] (rowpre[ty][TX] is the
-// row's count) and its entries of the ascending list of selected tiles (the
-// tiles not selected fill the list from the end, descending).  The
-// list offset of the row, the selected tiles of the rows above, is counted
-// by the block itself from the occluded and unmatched flags (a few KB read
-// from cache), so no second launch waits for the other rows.  The last row
-// also stores the total.
-__global__ __launch_bounds__(256) void select_kernel(int TX, int TY, int mode, const uint8_t *oc,
-                                                     const uint8_t *um, uint8_t *sel,
-                                                     uint32_t *rowpre, int *sel_list, int *sel_cols,
-                                                     uint8_t *mask_out, Counters *cnt) {
-    __shared__ uint32_t s_wave[4];
-    const int ty = blockIdx.x;
-    // selected tiles above the row: four flags per 32-bit word, then a byte tail
-    const uint32_t above = (uint32_t)ty * (uint32_t)TX;
-    uint32_t part = 0;
-    if (mode) {
-        part = threadIdx.x == 0 ? above : 0u;
-    } else {
-        const uint32_t nw = above / 4u;
-        const uint32_t *ow = reinterpret_cast<const uint32_t *>(oc);
-        const uint32_t *uw = reinterpret_cast<const uint32_t *>(um);
-        for (uint32_t k = threadIdx.x; k < nw; k += 256) {
-            const uint32_t f = (ow[k] | uw[k]) & 0x01010101u;   // flags are 0 or 1
-            part += (f * 0x01010101u) >> 24;
+// One block per tile row ty: selected = occluded | unmatched (or every
+// tile), row ty + 1 of the mask's summed area table (block 0 also row 0), the
+// columns of the row's selected tiles in order, and its entries of the
+// ascending list of selected tiles (the tiles not selected fill the list from
+// the end, descending).  What lies above the row the block counts itself from
+// the flags, per column (threads share out the rows above, a few KB read from
+// cache), so no second launch waits for the other rows.  The last row also
+// stores the total.
+constexpr int kSelThreads = 512;
+constexpr int kSelWaves = kSelThreads / 64;
+
+// Exclusive scans across the block of two values per thread; totals in ta, tb.
+__device__ inline void select_scan2(uint32_t &a, uint32_t &b, uint2 *s_wave, uint32_t &ta, uint32_t &tb) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t ia = a, ib = b;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t xa = __shfl_up(ia, d), xb = __shfl_up(ib, d);
+        if (lane >= d) {
+            ia += xa;
+            ib += xb;
         }
-        for (uint32_t t = 4u * nw + threadIdx.x; t < above; t += 256) part += (uint32_t)(oc[t] | um[t]);
     }
-    uint32_t off;
-    (void)block_exclusive_scan256(part, s_wave, &off);
-    uint32_t *row = rowpre + (size_t)ty * (TX + 1);
-    uint32_t run = 0;
-    for (int c = 0; c < TX; c += 256) {
-        const int x = c + threadIdx.x;
-        const int t = ty * TX + x;
-        uint32_t f = 0;
+    if (lane == 63) s_wave[wave] = make_uint2(ia, ib);
+    __syncthreads();
+    uint32_t oa = 0, ob = 0;
+    ta = tb = 0;
+#pragma unroll
+    for (int w = 0; w < kSelWaves; ++w) {
+        const uint2 x = s_wave[w];
+        if (w < wave) {
+            oa += x.x;
+            ob += x.y;
+        }
+        ta += x.x;
+        tb += x.y;
+    }
+    __syncthreads();
+    a = oa + ia - a;
+    b = ob + ib - b;
+}
+
+__global__ __launch_bounds__(kSelThreads) void select_kernel(int TX, int TY, int mode, const uint8_t *oc,
+                                                             const uint8_t *um, uint8_t *sel,
+                                                             uint32_t *sat, int *sel_list, int *sel_cols,
+                                                             uint8_t *mask_out, Counters *cnt) {
+    __shared__ uint32_t s_col[kSelThreads];
+    __shared__ uint2 s_wave[kSelWaves];
+    const int ty = blockIdx.x, tid = threadIdx.x;
+    // a chunk of 2^cb columns (the grid's width or 512) by 512 >> cb groups of rows
+    int cb = 4;
+    while (cb < 9 && (1 << cb) < TX) ++cb;
+    const int cw = 1 << cb, groups = kSelThreads >> cb;
+    const int xi = tid & (cw - 1), grp = tid >> cb;
+    // selected tiles of the chunk's columns above the row; valid for tid < cw
+    auto above_of = [&](int c0) -> uint32_t {
+        const int x = c0 + xi;
+        uint32_t part = 0;
         if (x < TX) {
+            if (mode) {
+                part = grp == 0 ? (uint32_t)ty : 0u;
+            } else {
+                int y = grp;
+                for (; y + 7 * groups < ty; y += 8 * groups) {
+                    uint32_t f[8];
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) {
+                        const size_t t = (size_t)(y + k * groups) * TX + x;
+                        f[k] = (uint32_t)(oc[t] | um[t]);
+                    }
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) part += f[k];
+                }
+                for (; y < ty; y += groups) {
+                    const size_t t = (size_t)y * TX + x;
+                    part += (uint32_t)(oc[t] | um[t]);
+                }
+            }
+        }
+        __syncthreads();
+        s_col[tid] = part;
+        __syncthreads();
+        uint32_t a = 0;
+        if (tid < cw)
+            for (int g = 0; g < groups; ++g) a += s_col[g * cw + tid];
+        return a;
+    };
+    uint32_t off = 0;   // selected tiles above the row
+    if (TX > cw) {      // block-uniform; else known from the one chunk's scan
+        for (int c0 = 0; c0 < TX; c0 += cw) {
+            uint32_t a = above_of(c0), z = 0, ta, tz;
+            select_scan2(a, z, s_wave, ta, tz);
+            off += ta;
+        }
+    }
+    const uint32_t above = (uint32_t)ty * (uint32_t)TX;
+    uint32_t *row = sat + (size_t)(ty + 1) * (TX + 1);
+    uint32_t run = 0, run_sat = 0;   // of the chunks before
+    for (int c0 = 0; c0 < TX; c0 += cw) {
+        const int x = c0 + tid;
+        const bool mine = tid < cw && x < TX;
+        const int t = ty * TX + x;
+        uint32_t a = above_of(c0), f = 0;
+        if (mine) {
             f = mode ? 1u : (uint32_t)(oc[t] | um[t]);
             sel[t] = (uint8_t)f;
             if (mask_out) mask_out[t] = (uint8_t)f;
         }
-        uint32_t tot;
-        const uint32_t ex = block_exclusive_scan256(f, s_wave, &tot);
-        if (x < TX) {
-            row[x] = run + ex;
+        uint32_t ex = f, exs = a + f, tot, tots;
+        select_scan2(ex, exs, s_wave, tot, tots);
+        if (TX <= cw) off = tots - tot;
+        if (mine) {
+            row[x] = run_sat + exs;
+            if (ty == 0) sat[x] = 0u;
             if (f) {
                 sel_list[off + run + ex] = t;
                 sel_cols[(size_t)ty * TX + run + ex] = x;
@@ -279,9 +325,11 @@ __global__ __launch_bounds__(256) void select_kernel(int TX, int TY, int mode, c
             }
         }
         run += tot;
+        run_sat += tots;
     }
-    if (threadIdx.x == 0) {
-        row[TX] = run;
+    if (tid == 0) {
+        row[TX] = run_sat;
+        if (ty == 0) sat[TX] = 0u;
         if (ty == TY - 1) cnt->n_selected = off + run;
     }
 }
@@ -325,9 +373,9 @@ void launch_occluded(const WarpK &w, int n, const uint8_t *status, const float4 
 }
 
 void launch_select(int TX, int TY, int mode, const uint8_t *oc, const uint8_t *um, uint8_t *sel,
-                   int *sel_list, uint32_t *rowpre, int *sel_cols, uint8_t *mask_out,
+                   int *sel_list, uint32_t *sat, int *sel_cols, uint8_t *mask_out,
                    Counters *cnt, hipStream_t st) {
-    select_kernel<<<TY, 256, 0, st>>>(TX, TY, mode, oc, um, sel, rowpre, sel_list, sel_cols,
+    select_kernel<<<TY, kSelThreads, 0, st>>>(TX, TY, mode, oc, um, sel, sat, sel_list, sel_cols,
                                       mask_out, cnt);
 }
 

@@ -90,7 +90,7 @@ struct Workspace {
     DevBuf g, rect, status, count, partial;
     DevBuf dkey, didx, dkey_alt, didx_alt, offs;
     DevBuf tkey, tval, tkey_alt, tval_alt, sort, segments, kfirst;
-    DevBuf ranges, tile_len, sel, sel_list, sel_cols, rowpre, cnt, tile_order;
+    DevBuf ranges, tile_len, sel, sel_list, sel_cols, sat, cnt, tile_order;
     HostCounters *host_cnt = nullptr;     // coherent pinned memory, written by the device
     HostCounters *host_cnt_dev = nullptr; // its device-side address
     // pinned: longest tile list's log2 bucket of some recent frame, [0] of
@@ -147,13 +147,14 @@ struct Workspace {
         }
         if (W_ != W || H_ != H) {
             const size_t nt = (size_t)TX * TY;
-            TGS_TRY(ranges.ensure(nt * sizeof(uint2)));
-            TGS_TRY(tile_len.ensure(nt * sizeof(uint32_t)));
+            // the tiles' ranges, then their lengths
+            TGS_TRY(ranges.ensure(nt * (sizeof(uint2) + sizeof(uint32_t))));
+            tile_len.borrow(ranges.as<uint2>() + nt, nt * sizeof(uint32_t));
             TGS_TRY(sel.ensure(nt));
             TGS_TRY(sel_list.ensure(nt * sizeof(int)));
             TGS_TRY(tile_order.ensure(nt * sizeof(int)));
             TGS_TRY(sel_cols.ensure(nt * sizeof(int)));
-            TGS_TRY(rowpre.ensure((size_t)TY * (TX + 1) * sizeof(uint32_t)));
+            TGS_TRY(sat.ensure((size_t)(TY + 1) * (TX + 1) * sizeof(uint32_t)));
             W = W_;
             H = H_;
         }
@@ -423,7 +424,7 @@ constexpr int kSegSmallScene = 131072;
 // keys are emitted: depth order (global depth sort; the last pass publishes
 // the frame's counters to the host, tag ws.seq) or index order (count scan,
 // each tile's list sorted by depth after the tile sort).  Nothing here waits.
-tgs_status step_scan(const tgs_scene *sc, Workspace &ws, const uint32_t *rowpre, int TX,
+tgs_status step_scan(const tgs_scene *sc, Workspace &ws, const uint32_t *sat, int TX,
                      hipStream_t st, const uint32_t **sorted_didx) {
     const int n = sc->n;
     // per frame: the per-tile sort pays off in selective-rendering frames
@@ -432,16 +433,16 @@ tgs_status step_scan(const tgs_scene *sc, Workspace &ws, const uint32_t *rowpre,
     // the depth sort sorts Gaussians, and takes the global depth sort
     // (and in every frame of a small scene: below kSegSmallScene Gaussians the
     // four depth passes are launch latency, not work)
-    const uint32_t maxb = ws.host_maxb ? reinterpret_cast<volatile uint32_t *>(ws.host_maxb)[rowpre ? 1 : 0]
+    const uint32_t maxb = ws.host_maxb ? reinterpret_cast<volatile uint32_t *>(ws.host_maxb)[sat ? 1 : 0]
                                        : 0xffffffffu;
     ws.frame_seg = sc->sort_path == TGS_SORT_PER_TILE ||
-                   (sc->sort_path == TGS_SORT_AUTO && (rowpre != nullptr || n < kSegSmallScene) &&
+                   (sc->sort_path == TGS_SORT_AUTO && (sat != nullptr || n < kSegSmallScene) &&
                     maxb <= (uint32_t)kSegBucketMax);
     if (ws.frame_seg) {
         ProfScope ps(TGS_PROF_SORT, st);
         ws.seq += 1;
         uint32_t *part = ws.sort.as<uint32_t>();
-        launch_count_scan(n, ws.count.as<uint32_t>(), ws.rect.as<ushort4>(), rowpre, TX, part,
+        launch_count_scan(n, ws.count.as<uint32_t>(), ws.rect.as<ushort4>(), sat, TX, part,
                           ws.didx.as<uint32_t>(), ws.offs.as<uint32_t>(), ws.kfirst.as<uint32_t>(),
                           ws.cnt.as<Counters>(), (uint32_t)ws.key_cap, ws.partial.as<uint32_t>(),
                           n > 0 ? preprocess_blocks(n) : 0, ws.host_cnt_dev, ws.seq, st);
@@ -452,7 +453,7 @@ tgs_status step_scan(const tgs_scene *sc, Workspace &ws, const uint32_t *rowpre,
     {
         ProfScope ps(TGS_PROF_SORT, st);
         ws.seq += 1;
-        launch_depth_sort(n, ws.count.as<uint32_t>(), ws.rect.as<ushort4>(), rowpre, TX,
+        launch_depth_sort(n, ws.count.as<uint32_t>(), ws.rect.as<ushort4>(), sat, TX,
                           ws.dkey.as<uint32_t>(),
                           ws.dkey_alt.as<uint32_t>(), ws.didx_alt.as<uint32_t>(),
                           ws.dkey.as<uint32_t>(), ws.didx.as<uint32_t>(), ws.offs.as<uint32_t>(),
@@ -520,7 +521,7 @@ int tile_id_bits(int TX, int TY) {
 
 // Emit the keys in depth order, sort them by tile (stable), find tile ranges;
 // returns the per-tile lists of Gaussian indices.
-tgs_status step_keys(const tgs_scene *sc, Workspace &ws, int TX, int TY, const uint32_t *rowpre,
+tgs_status step_keys(const tgs_scene *sc, Workspace &ws, int TX, int TY, const uint32_t *sat,
                      const int *sel_cols, const uint32_t *didx, hipStream_t st,
                      const uint32_t **sorted_vals) {
     const int n = sc->n;
@@ -528,7 +529,7 @@ tgs_status step_keys(const tgs_scene *sc, Workspace &ws, int TX, int TY, const u
     Counters *cnt = ws.cnt.as<Counters>();
     // expected keys: those of the last frame of the kind, else (a first frame,
     // an allocation-free call) the first guess of the key capacity
-    uint32_t hint = ws.recent_K[rowpre ? 1 : 0];
+    uint32_t hint = ws.recent_K[sat ? 1 : 0];
     if (hint == kUnknownKeys) hint = (uint32_t)std::min<size_t>(cap, 4 * (size_t)n + 65536);
     TileSortPlan tp = tile_sort_plan(n, tile_id_bits(TX, TY));
     if (ws.general) tp.packed = false;
@@ -540,7 +541,7 @@ tgs_status step_keys(const tgs_scene *sc, Workspace &ws, int TX, int TY, const u
     {
         ProfScope ps(TGS_PROF_DUPLICATE, st);
         launch_duplicate(n, cap, cnt, didx, ws.offs.as<uint32_t>(), ws.kfirst.as<uint32_t>(),
-                         ws.rect.as<ushort4>(), rowpre, sel_cols, TX, TX * TY, tp,
+                         ws.rect.as<ushort4>(), sat, sel_cols, TX, TX * TY, tp,
                          ws.tkey.as<uint32_t>(), ws.tval.as<uint32_t>(), ws.ranges.as<uint2>(),
                          ws.tile_len.as<uint32_t>(),
                          counted ? sort_count_rows(ws.sort.as<uint32_t>()) : nullptr, st);
@@ -549,11 +550,11 @@ tgs_status step_keys(const tgs_scene *sc, Workspace &ws, int TX, int TY, const u
     // blend order: the selected tiles, or all of them, longest lists first
     OrderK order{};
     order.n_host = TX * TY;
-    order.n_dev = rowpre ? &cnt->n_selected : nullptr;
-    order.tile_in = rowpre ? ws.sel_list.as<int>() : nullptr;
+    order.n_dev = sat ? &cnt->n_selected : nullptr;
+    order.tile_in = sat ? ws.sel_list.as<int>() : nullptr;
     order.ranges = ws.ranges.as<uint2>();
     order.tile_out = ws.tile_order.as<int>();
-    order.max_bucket = ws.host_maxb_dev + (rowpre ? 1 : 0);
+    order.max_bucket = ws.host_maxb_dev + (sat ? 1 : 0);
     order.n_split = &cnt->n_split;
     order.split_bucket = sc->split_bucket;
     order.max_split = sc->split_max;
@@ -590,7 +591,7 @@ tgs_status step_keys(const tgs_scene *sc, Workspace &ws, int TX, int TY, const u
         // frame of the same kind had any (the longest list's bucket, from the
         // host copy)
         const uint32_t maxb = ws.host_maxb
-            ? reinterpret_cast<volatile uint32_t *>(ws.host_maxb)[rowpre ? 1 : 0] : 0xffffffffu;
+            ? reinterpret_cast<volatile uint32_t *>(ws.host_maxb)[sat ? 1 : 0] : 0xffffffffu;
         launch_segment_sort(TX * TY, ws.ranges.as<uint2>(), svals,
                             alt ? ws.tval.as<uint32_t>() : ws.tval_alt.as<uint32_t>(),
                             ws.dkey.as<uint32_t>(), maxb >= (uint32_t)kSegLongBucket, st);
@@ -995,7 +996,7 @@ bool layout_full(Workspace &ws, char *base, size_t cap, int n, int W, int H, siz
               c.take(ws.ranges, nt * sizeof(uint2)) && c.take(ws.sel, nt) &&
               c.take(ws.sel_list, nt * sizeof(int)) && c.take(ws.tile_order, nt * sizeof(int)) &&
               c.take(ws.sel_cols, nt * sizeof(int)) &&
-              c.take(ws.rowpre, (size_t)TY * (TX + 1) * sizeof(uint32_t)) &&
+              c.take(ws.sat, (size_t)TY * (TX + 1) * sizeof(uint32_t)) &&
               c.take(ws.cnt, sizeof(Counters)) && c.take(ws.sort, sort_words * sizeof(uint32_t)) &&
               c.take(ws.tkey, packed ? key_cap + 16 : key_cap * 4) && c.take(ws.tval, key_cap * 4) &&
               (packed ? c.take(ws.segments, tile_sort_segment_words((uint32_t)key_cap) * 4) &&
@@ -1256,13 +1257,13 @@ tgs_status tgs_render_temporal(tgs_state *s, const tgs_camera *cam, tgs_frame_ou
             {
                 ProfScope ps(TGS_PROF_SELECT, st);
                 launch_select(TX, TY, mode, s->oc.as<uint8_t>(), s->um.as<uint8_t>(),
-                              ws.sel.as<uint8_t>(), ws.sel_list.as<int>(), ws.rowpre.as<uint32_t>(),
+                              ws.sel.as<uint8_t>(), ws.sel_list.as<int>(), ws.sat.as<uint32_t>(),
                               ws.sel_cols.as<int>(), out->tile_mask, ws.cnt.as<Counters>(), st);
                 TGS_LAUNCHED("tile selection");
             }
             const uint32_t *didx = nullptr;
-            TGS_TRY(step_scan(sc, ws, ws.rowpre.as<uint32_t>(), TX, st, &didx));
-            TGS_TRY(step_keys(sc, ws, TX, TY, ws.rowpre.as<uint32_t>(), ws.sel_cols.as<int>(), didx,
+            TGS_TRY(step_scan(sc, ws, ws.sat.as<uint32_t>(), TX, st, &didx));
+            TGS_TRY(step_keys(sc, ws, TX, TY, ws.sat.as<uint32_t>(), ws.sel_cols.as<int>(), didx,
                               st, &vals));
             BlendArgs a = blend_args(ws, cam, vals);
             set_blend_order(a, ws, sc);

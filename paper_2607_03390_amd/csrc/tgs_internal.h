@@ -120,27 +120,15 @@ __device__ inline float ordered_to_float(int i) {
 }
 
 // Key count of a Gaussian in a selective-rendering frame: the selected tiles
-// of its rectangle, from per-row prefix sums of the tile mask (rowpre, TY
-// rows of TX + 1 entries; one subtraction per row).
-__device__ inline uint32_t masked_count(ushort4 r, const uint32_t *rowpre, int TX) {
+// of its rectangle, from the tile mask's summed area table: sat[y * (TX + 1)
+// + x] = selected tiles in rows below y and columns below x (TY + 1 rows), so
+// four loads whatever the rectangle's height.  (From prefix sums per row, two
+// loads a row, counting 1.5M Gaussians took 11.9 us and 3M needles 66 us.)
+__device__ inline uint32_t masked_count(ushort4 r, const uint32_t *sat, int TX) {
     if (r.x > r.z || r.y > r.w) return 0u;
-    uint32_t c = 0;
-    int y = r.y;
-    // four rows per step: all eight loads are in flight before the first use
-    for (; y + 3 <= (int)r.w; y += 4) {
-        const uint32_t *row = rowpre + (size_t)y * (TX + 1);
-        const size_t s = (size_t)(TX + 1);
-        const uint32_t a0 = row[r.z + 1], b0 = row[r.x];
-        const uint32_t a1 = row[s + r.z + 1], b1 = row[s + r.x];
-        const uint32_t a2 = row[2 * s + r.z + 1], b2 = row[2 * s + r.x];
-        const uint32_t a3 = row[3 * s + r.z + 1], b3 = row[3 * s + r.x];
-        c += (a0 - b0) + (a1 - b1) + (a2 - b2) + (a3 - b3);
-    }
-    for (; y <= (int)r.w; ++y) {
-        const uint32_t *row = rowpre + (size_t)y * (TX + 1);
-        c += row[r.z + 1] - row[r.x];
-    }
-    return c;
+    const uint32_t *top = sat + (size_t)r.y * (TX + 1), *bot = sat + (size_t)(r.w + 1) * (TX + 1);
+    const uint32_t t0 = top[r.x], t1 = top[r.z + 1], b0 = bot[r.x], b1 = bot[r.z + 1];
+    return (b1 - b0) - (t1 - t0);
 }
 
 // ---- launchers (k_preprocess.hip) ----
@@ -174,7 +162,7 @@ __device__ inline void mark_key_blocks(uint32_t *kfirst, uint32_t nb, uint32_t s
 // Emits the cnt->n_sorted keys of the cnt->n_visible depth-ordered Gaussians
 // (cap bounds n_sorted for the grid; nothing is emitted past the key
 // capacity) and clears the tile ranges and lengths (filled by the tile sort, or
-// the ranges by launch_ranges after it).  rowpre / sel_cols are NULL in frames that render every tile.
+// the ranges by launch_ranges after it).  sat / sel_cols are NULL in frames that render every tile.
 // Keys: tile id to tkey and index to tval, or (tp.packed) the low digit bytes
 // to tkey and the payload to tval (launch_tile_sort).  rows (optional): per
 // block of kKeyBlock keys, the counts of the low digit in row b of
@@ -182,7 +170,7 @@ __device__ inline void mark_key_blocks(uint32_t *kfirst, uint32_t nb, uint32_t s
 struct TileSortPlan;
 void launch_duplicate(int n, uint32_t cap, const Counters *cnt, const uint32_t *didx,
                       const uint32_t *offs, const uint32_t *kfirst, const ushort4 *rect,
-                      const uint32_t *rowpre, const int *sel_cols, int TX, int n_tiles,
+                      const uint32_t *sat, const int *sel_cols, int TX, int n_tiles,
                       const TileSortPlan &tp, uint32_t *tkey, uint32_t *tval, uint2 *ranges,
                       uint32_t *tile_len, uint32_t *rows, hipStream_t st);
 // Ranges of the cnt->n_sorted tile-sorted keys; cap bounds n_sorted for the grid.
@@ -271,14 +259,14 @@ int launch_tile_sort(const TileSortPlan &tp, uint32_t cap, uint32_t n_hint, cons
 
 // Depth order of the Gaussians with count[i] > 0 among i < n, stable by index
 // (keys dkey[i], the depth's float bits): four passes (dkey -> a -> b -> a ->
-// v_b; k_b may alias dkey).  With rowpre (a selective-rendering frame) the
+// v_b; k_b may alias dkey).  With sat (a selective-rendering frame) the
 // first pass first replaces count[i] by the masked count of rect[i].  Writes cnt->n_visible (Gaussians kept), the
 // sorted indices to v_b[0..n_visible), offs[s] = exclusive prefix of their
 // counts and the key-block owners kfirst[0 .. key_blocks(cap)), then
 // cnt->n_keys, cnt->n_sorted (n_keys if <= cap, else 0),
 // cnt->n_survivors / n_newly (from the preprocess partials) and, tag last,
 // the same counters to `host`.
-void launch_depth_sort(int n, uint32_t *count, const ushort4 *rect, const uint32_t *rowpre, int TX,
+void launch_depth_sort(int n, uint32_t *count, const ushort4 *rect, const uint32_t *sat, int TX,
                        const uint32_t *dkey, uint32_t *k_a, uint32_t *v_a, uint32_t *k_b,
                        uint32_t *v_b, uint32_t *offs, uint32_t *kfirst, uint32_t *scratch,
                        Counters *cnt, uint32_t cap, const uint32_t *pre_partial, int n_pre,
@@ -292,7 +280,7 @@ void launch_depth_sort(int n, uint32_t *count, const ushort4 *rect, const uint32
 // does; after the tile sort, each tile's list sorted by (depth bits, index)
 // in place (tmp: scratch of the same size as vals).
 int count_scan_blocks(int n);
-void launch_count_scan(int n, uint32_t *count, const ushort4 *rect, const uint32_t *rowpre, int TX,
+void launch_count_scan(int n, uint32_t *count, const ushort4 *rect, const uint32_t *sat, int TX,
                        uint32_t *part, uint32_t *vidx, uint32_t *voffs, uint32_t *kfirst,
                        Counters *cnt, uint32_t cap, const uint32_t *pre_partial, int n_pre,
                        HostCounters *host, uint32_t tag, hipStream_t st);
@@ -400,10 +388,11 @@ void launch_fill_query(const FillK &f, hipStream_t st);
 void launch_occluded(const WarpK &w, int n, const uint8_t *status, const float4 *g,
                      const ushort4 *rect, uint8_t *oc, hipStream_t st);
 // sel_list: the selected tiles ascending in [0, n_selected), the others
-// descending from the end (a permutation of all tiles);
+// descending from the end (a permutation of all tiles); sat: the mask's
+// summed area table ((TY + 1) x (TX + 1), see masked_count);
 // sel_cols[ty * TX + k] = column of the k-th selected tile of row ty
 void launch_select(int TX, int TY, int mode, const uint8_t *oc, const uint8_t *um, uint8_t *sel,
-                   int *sel_list, uint32_t *rowpre, int *sel_cols, uint8_t *mask_out,
+                   int *sel_list, uint32_t *sat, int *sel_cols, uint8_t *mask_out,
                    Counters *cnt, hipStream_t st);
 void launch_fill_u8(uint8_t *p, size_t n, uint8_t v, hipStream_t st);
 void launch_fill_f32(float *p, size_t n, float v, hipStream_t st);

@@ -131,11 +131,22 @@ __global__ __launch_bounds__(kOccThreads) void occluded_kernel(WarpK w, int n,
     __shared__ uint32_t s_wave[kOccWaves];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int i0 = blockIdx.x * kOccBlock + tid * kOccPer;
+    // the four status bytes in one load (their buffer is four-byte aligned)
+    uint32_t st = 0u;
+    if (i0 + kOccPer <= n) {
+        st = *reinterpret_cast<const uint32_t *>(status + i0);
+    } else {
+#pragma unroll
+        for (int k = 0; k < kOccPer; ++k)
+            if (i0 + k < n) st |= (uint32_t)status[i0 + k] << (8 * k);
+    }
+    st &= 0x02020202u;
+    if (!__syncthreads_or((int)st)) return;   // most blocks: nothing newly visible
     uint32_t c[kOccPer], na = 0u, np = 0u;
 #pragma unroll
     for (int k = 0; k < kOccPer; ++k) {
         c[k] = 0u;
-        if (i0 + k < n && (status[i0 + k] & 2u)) {
+        if (st >> (8 * k) & 2u) {
             int3 box;
             c[k] = occ_box(i0 + k, g, rect, &box);
         }
@@ -160,6 +171,7 @@ __global__ __launch_bounds__(kOccThreads) void occluded_kernel(WarpK w, int n,
         const uint32_t r = r0 + (uint32_t)lane;
         int tx = 0, ty = 0;
         float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f), b = a;
+        bool test = false;
         if (r < mine) {
             const uint32_t p = (uint32_t)wave + kOccWaves * r;
             // owner of pair p: the last entry whose start is <= p (starts
@@ -178,9 +190,27 @@ __global__ __launch_bounds__(kOccThreads) void occluded_kernel(WarpK w, int n,
             ty = box.y + k / box.z;
             a = g[4 * (size_t)gi];
             b = g[4 * (size_t)gi + 1];
+            // Left out: tiles already marked (a mark seen late only costs
+            // the test), and tiles whose centre lies farther from the mean
+            // than sqrt(k) + m in the norm of the conic (m: the tile's
+            // centre-to-corner offset (7.5, +-7.5); k >= 2 ln(255 o) from
+            // the record): by the triangle inequality no pixel centre of
+            // theirs reaches alpha >= 1/255.  Enlarged by 0.2 % + 0.01 and by
+            // the rounding of the exponent (below) at the tile's pixels and of
+            // q here: its terms cancel along a needle, eight roundings of
+            // at most 2^-24 of their sum, itself at most 2 (T + m^2) at a
+            // pixel.  A needle's box has many more tiles than its ellipse
+            // meets.
+            const float kq = g[4 * (size_t)gi + 3].w;
+            const float m2 = 56.25f * (a.z + b.x + 2.0f * fabsf(a.w));
+            const float dx = (float)(tx * kTile) + 7.5f - a.x, dy = (float)(ty * kTile) + 7.5f - a.y;
+            const float sq = a.z * dx * dx + b.x * dy * dy, cross = 2.0f * a.w * dx * dy;
+            const float err = 2e-6f * ((sq + fabsf(cross)) + m2);
+            const float rr = (__builtin_amdgcn_sqrtf(kq + err) + __builtin_amdgcn_sqrtf(m2)) * 1.002f + 0.01f;
+            test = !((sq + cross) - err > rr * rr) && !oc[ty * w.TX + tx];
         }
-        const int m = (int)min(64u, mine - r0);
-        for (int j = 0; j < m; ++j) {
+        for (uint64_t left = __ballot(test); left != 0ull; left &= left - 1ull) {
+            const int j = __ffsll((long long)left) - 1;
             const int jx = __builtin_amdgcn_readlane(tx, j), jy = __builtin_amdgcn_readlane(ty, j);
             const float ax = lane_f(a.x, j), ay = lane_f(a.y, j), az = lane_f(a.z, j),
                         aw = lane_f(a.w, j), bx = lane_f(b.x, j), by = lane_f(b.y, j);

@@ -321,18 +321,17 @@ tgs_status tgs_profile_stop(tgs_profile *out);
  * tile) is produced, for every later render through `scene` (tgs_render_full
  * and the temporal states bound to it).  Both ways give identical per-tile
  * lists (depth bits, then Gaussian index):
- *   TGS_SORT_DEPTH_FIRST: the Gaussians with keys are radix-sorted by depth
- *     (four passes of at most 8 bits over them), keys are emitted in that order and
- *     stably radix-sorted by tile;
+ *   TGS_SORT_DEPTH_FIRST: the Gaussians with keys are sorted by depth (a
+ *     sample sort; radix passes above 2^23 Gaussians), keys are emitted in
+ *     that order and stably radix-sorted by tile;
  *   TGS_SORT_PER_TILE: key counts are scanned in index order, keys emitted
  *     in index order and stably sorted by tile, then one block per tile
  *     sorts its list by (depth bits, index) in LDS (lists above 4096 entries
  *     take a slower in-block path);
- *   TGS_SORT_AUTO (default): per frame, the per-tile sort for TemporalGS
- *     frames (keys on the selected tiles only), and for every frame of a
- *     scene with fewer than 131072 Gaussians, when the longest tile list of
- *     a recent frame of the same kind has fewer than 4096 entries; else the
- *     depth-first sort.
+ *   TGS_SORT_AUTO (default): per frame, the per-tile sort for scenes with
+ *     fewer than 8192 Gaussians (and for TemporalGS frames above 2^23), when
+ *     the longest tile list of a recent frame of the same kind has fewer than
+ *     4096 entries; else the depth-first sort.
  * INVALID_ARG for a NULL scene or another value.  Like every call on a
  * scene, it must not overlap with renders through it. */
 enum { TGS_SORT_AUTO = 0, TGS_SORT_DEPTH_FIRST = 1, TGS_SORT_PER_TILE = 2 };

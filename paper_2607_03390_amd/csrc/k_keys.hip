@@ -90,6 +90,7 @@ struct DupIo {
     const uint32_t *offs;
     const uint32_t *kfirst;
     const ushort4 *rect;
+    bool rect_sorted;   // in emission order, not by index
     const uint32_t *sat;
     const int *sel_cols;
     int TX;
@@ -117,16 +118,17 @@ __device__ inline void dup_window(const DupIo &io, uint32_t P0, uint32_t P1, uin
 // Owners of the output positions [P0, P1) by a block of NT threads: s_off[k]
 // / s_g[k] = start and Gaussian index of window entry k (those starting
 // before P1), own[i] = the window entry owning position P0 + kPer tid + i
-// (kPer consecutive positions per thread; past P1: the last entry).  The
-// window is read in one step (every load in flight at once).
+// (kPer consecutive positions per thread; past P1: the last entry), j0 = the
+// emission position of entry 0.  The window is read in one step (every load
+// in flight at once).
 template <int KD, int NT>
 __device__ inline void dup_owners(const DupIo &io, uint32_t P0, uint32_t P1, uint32_t K,
                                   uint32_t V, int *s_mark, uint32_t *s_off, uint32_t *s_g,
-                                  int *s_wmax, int (&own)[KD / NT]) {
+                                  int *s_wmax, int (&own)[KD / NT], uint32_t &j0) {
     static_assert(KD % NT == 0 && KD % kKeyBlock == 0, "whole steps and key blocks");
     constexpr int kPer = KD / NT;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    uint32_t j0, nw;
+    uint32_t nw;
     dup_window<KD>(io, P0, P1, K, V, j0, nw);
     // clamped indices, no branches: every load is issued before the first wait
     uint32_t o[kPer], g[kPer];
@@ -207,7 +209,8 @@ __global__ __launch_bounds__(256) void duplicate_kernel(DupIo io, uint32_t *tkey
     constexpr int kPer = kDupKeys / 256;
     static_assert(kPer == 4, "four keys per 16-byte store");
     int own[kPer];
-    dup_owners<kDupKeys, 256>(io, P0, P1, K, V, s_mark, s_off, s_g, s_wmax, own);
+    uint32_t j0;
+    dup_owners<kDupKeys, 256>(io, P0, P1, K, V, s_mark, s_off, s_g, s_wmax, own, j0);
     // positions past the keys take the last key's (no branch before the
     // stores, so every rectangle load is in flight together)
     const uint32_t p = P0 + (uint32_t)(kPer * tid);
@@ -218,7 +221,7 @@ __global__ __launch_bounds__(256) void duplicate_kernel(DupIo io, uint32_t *tkey
         const uint32_t pc = p + k < P1 ? p + k : P1 - 1u;
         g[k] = s_g[own[k]];
         r[k] = pc - s_off[own[k]];
-        rc[k] = io.rect[g[k]];
+        rc[k] = io.rect[io.rect_sorted ? j0 + (uint32_t)own[k] : g[k]];
     }
     KeyWalk walk;
 #pragma unroll
@@ -320,7 +323,7 @@ __global__ __launch_bounds__(256) void order_tiles_kernel(OrderK o) {
 
 void launch_duplicate(int n, uint32_t cap, const Counters *cnt, const uint32_t *didx,
                       const uint32_t *offs, const uint32_t *kfirst, const ushort4 *rect,
-                      const uint32_t *sat, const int *sel_cols, int TX, int n_tiles,
+                      bool rect_sorted, const uint32_t *sat, const int *sel_cols, int TX, int n_tiles,
                       const TileSortPlan &tp, uint32_t *tkey, uint32_t *tval, uint2 *ranges,
                       uint32_t *tile_len, uint32_t *rows, hipStream_t st) {
     if (n <= 0 || cap == 0) {
@@ -329,7 +332,7 @@ void launch_duplicate(int n, uint32_t cap, const Counters *cnt, const uint32_t *
         return;
     }
     const uint32_t blocks = (cap + kDupKeys - 1) / kDupKeys;
-    const DupIo io{cnt, didx, offs, kfirst, rect, sat, sel_cols, TX, n_tiles, ranges,
+    const DupIo io{cnt, didx, offs, kfirst, rect, rect_sorted, sat, sel_cols, TX, n_tiles, ranges,
                    tile_len, rows, tp.lo, tp.index_bits};
     if (tp.packed) duplicate_kernel<true><<<blocks, 256, 0, st>>>(io, tkey, tval);
     else duplicate_kernel<false><<<blocks, 256, 0, st>>>(io, tkey, tval);

@@ -247,7 +247,12 @@ __global__ __launch_bounds__(256) void preprocess_kernel(SceneDev s, CamK cam, C
         }
         rec.rect[i] = rect;
         rec.count[i] = keys;
-        rec.dkey[i] = __float_as_uint(tz);
+        const uint32_t dk = keys ? __float_as_uint(tz) : kNoDepth;
+        rec.dkey[i] = dk;
+        if (rec.samples) {
+            const uint32_t q = (uint32_t)((uint64_t)i * rec.sample_magic >> 40);
+            if ((uint32_t)i == depth_sample_at(q, rec.sample_stride, s.n)) rec.samples[q] = dk;
+        }
         rec.status[i] = (uint8_t)((survivor ? 1 : 0) | (newly ? 2 : 0));
         if (cull.clear_flag) cull.clear_flag[i] = 0u;
     }

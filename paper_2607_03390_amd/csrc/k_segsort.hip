@@ -205,7 +205,7 @@ __global__ __launch_bounds__(kScanThreads) void count_emit_kernel(
         cnt->n_survivors = n_surv;
         cnt->n_newly = n_newly;
         // n_selected was written by the tile selection
-        publish_host(host, k32, n_surv, n_newly, cnt->n_selected, tot_n, sorted, tag);
+        publish_host(host, k32, n_surv, n_newly, cnt->n_selected, tot_n, sorted, 0u, tag);
     }
 }
 

@@ -280,7 +280,7 @@ __device__ void publish_counters(const DepthIo &io, uint64_t n_keys, uint32_t *s
         io.cnt->n_newly = newly;
         // n_visible and n_selected were written by earlier kernels
         publish_host(io.host, k32, surv, newly, io.cnt->n_selected, io.cnt->n_visible, sorted,
-                     io.tag);
+                     0u, io.tag);
     }
     __syncthreads();
 }

@@ -88,7 +88,9 @@ constexpr uint32_t kUnknownKeys = 0xffffffffu;
 // Per-frame scratch of one render path (a scene's tgs_render_full, or a state).
 struct Workspace {
     DevBuf g, rect, status, count, partial;
-    DevBuf dkey, didx, dkey_alt, didx_alt, offs;
+    DevBuf dkey, didx, offs;
+    DevBuf dkey_alt, didx_alt;            // of the radix passes by depth, allocated with the first
+    DevBuf dsort;                         // scratch of the sample sort by depth
     DevBuf tkey, tval, tkey_alt, tval_alt, sort, segments, kfirst;
     DevBuf ranges, tile_len, sel, sel_list, sel_cols, sat, cnt, tile_order;
     HostCounters *host_cnt = nullptr;     // coherent pinned memory, written by the device
@@ -97,6 +99,8 @@ struct Workspace {
     // frames that render every tile, [1] of selective-rendering frames
     uint32_t *host_maxb = nullptr;
     uint32_t *host_maxb_dev = nullptr;
+    bool radix_depth = false;             // depth order by radix passes, not by the sample sort
+    bool frame_samples = false;           // this frame's depth order is by the sample sort
     bool general = false;                 // keys as (tile id, index) words whatever the plan says
     bool frame_seg = false;               // this frame orders tiles by the per-tile sort
     uint32_t seq = 0;                     // tag of the last frame's counters
@@ -138,9 +142,8 @@ struct Workspace {
             TGS_TRY(partial.ensure((size_t)(2 * preprocess_blocks(n_ > 0 ? n_ : 1)) * sizeof(uint32_t)));
             TGS_TRY(dkey.ensure(nn * sizeof(uint32_t)));
             TGS_TRY(didx.ensure(nn * sizeof(uint32_t)));
-            TGS_TRY(dkey_alt.ensure(nn * sizeof(uint32_t)));
-            TGS_TRY(didx_alt.ensure(nn * sizeof(uint32_t)));
             TGS_TRY(offs.ensure(nn * sizeof(uint32_t)));
+            if (depth_plan(n_, 1).ok) TGS_TRY(dsort.ensure(depth_plan(n_, 1).words * 8));
             // the depth sort runs over at most n keys
             TGS_TRY(sort.ensure(sort_scratch_words((uint32_t)nn) * sizeof(uint32_t)));
             n = n_;
@@ -187,9 +190,13 @@ struct Workspace {
     }
 
     Records records() const {
+        const DepthPlan dp = depth_plan(n, 1);
         return Records{g.as<float4>(),
                        rect.as<ushort4>(),   status.as<uint8_t>(),  count.as<uint32_t>(),
-                       dkey.as<uint32_t>(),  partial.as<uint32_t>()};
+                       dkey.as<uint32_t>(),  partial.as<uint32_t>(),
+                       dp.ok && dsort.p ? depth_scratch(dp, n, dsort.p).samples : nullptr,
+                       (uint32_t)dp.stride,
+                       dp.ok ? ((1ull << 40) + dp.stride - 1) / (uint64_t)dp.stride : 0ull};
     }
 };
 
@@ -401,6 +408,7 @@ namespace {
 
 struct FrameResult {
     uint32_t K = 0, V = 0, n_surv = 0, n_newly = 0, n_sel = 0;
+    bool redo = false;   // render again with the radix passes by depth
 };
 
 // Zero the counters and run the per-Gaussian stage.
@@ -418,7 +426,12 @@ tgs_status step_preprocess(const tgs_scene *sc, Workspace &ws, const CamK &cam, 
     return TGS_OK;
 }
 
-constexpr int kSegSmallScene = 131072;
+// Scenes below this many Gaussians sort each tile's list instead of the
+// Gaussians by depth where the lists are short: one launch fewer.  (Full
+// render, per-tile and by depth: 2k Gaussians 41.6 and 43.6 us, 10k 49.3 and
+// 48.8, 60k 163 and 142, 130k 129 and 104; temporal interval of 1.5M 1928 and
+// 1755 us.)
+constexpr int kSegSmallScene = 8192;
 
 // The Gaussians that have keys and the start of their keys, in the order the
 // keys are emitted: depth order (global depth sort; the last pass publishes
@@ -427,17 +440,17 @@ constexpr int kSegSmallScene = 131072;
 tgs_status step_scan(const tgs_scene *sc, Workspace &ws, const uint32_t *sat, int TX,
                      hipStream_t st, const uint32_t **sorted_didx) {
     const int n = sc->n;
-    // per frame: the per-tile sort pays off in selective-rendering frames
-    // (keys only on the selected tiles) whose lists fit its LDS bound; a
-    // frame rendering every tile sorts 3-4 times as many keys per tile as
-    // the depth sort sorts Gaussians, and takes the global depth sort
-    // (and in every frame of a small scene: below kSegSmallScene Gaussians the
-    // four depth passes are launch latency, not work)
+    // per frame: the per-tile sort in small scenes, and, where the sample
+    // sort by depth does not reach (2^23 Gaussians), in selective-rendering
+    // frames, whose keys are few beside the Gaussians; in both where a recent
+    // frame's lists fit the per-tile sort's LDS bound
+    const DepthPlan dp = depth_plan(n, TX * ((ws.H + 15) / 16));
+    const bool prefer_seg = dp.ok ? n < kSegSmallScene : sat != nullptr;
     const uint32_t maxb = ws.host_maxb ? reinterpret_cast<volatile uint32_t *>(ws.host_maxb)[sat ? 1 : 0]
                                        : 0xffffffffu;
+    ws.frame_samples = false;
     ws.frame_seg = sc->sort_path == TGS_SORT_PER_TILE ||
-                   (sc->sort_path == TGS_SORT_AUTO && (sat != nullptr || n < kSegSmallScene) &&
-                    maxb <= (uint32_t)kSegBucketMax);
+                   (sc->sort_path == TGS_SORT_AUTO && prefer_seg && maxb <= (uint32_t)kSegBucketMax);
     if (ws.frame_seg) {
         ProfScope ps(TGS_PROF_SORT, st);
         ws.seq += 1;
@@ -450,8 +463,23 @@ tgs_status step_scan(const tgs_scene *sc, Workspace &ws, const uint32_t *sat, in
         *sorted_didx = ws.didx.as<uint32_t>();
         return TGS_OK;
     }
-    {
+    ws.frame_samples = dp.ok && ws.dsort.p && !ws.radix_depth;
+    if (ws.frame_samples) {
         ProfScope ps(TGS_PROF_SORT, st);
+        ws.seq += 1;
+        launch_depth_samplesort(dp, depth_scratch(dp, n, ws.dsort.p), n, ws.dkey.as<uint32_t>(),
+                                ws.rect.as<ushort4>(), sat, TX, ws.didx.as<uint32_t>(),
+                                ws.offs.as<uint32_t>(), ws.kfirst.as<uint32_t>(), ws.cnt.as<Counters>(),
+                                (uint32_t)ws.key_cap, ws.partial.as<uint32_t>(), preprocess_blocks(n),
+                                ws.host_cnt_dev, ws.seq, st);
+        TGS_LAUNCHED("depth order");
+    } else {
+        ProfScope ps(TGS_PROF_SORT, st);
+        if (!ws.dkey_alt.borrowed) {
+            const size_t nn = (size_t)(n > 0 ? n : 1);
+            TGS_TRY(ws.dkey_alt.ensure(nn * sizeof(uint32_t)));
+            TGS_TRY(ws.didx_alt.ensure(nn * sizeof(uint32_t)));
+        }
         ws.seq += 1;
         launch_depth_sort(n, ws.count.as<uint32_t>(), ws.rect.as<ushort4>(), sat, TX,
                           ws.dkey.as<uint32_t>(),
@@ -496,18 +524,23 @@ tgs_status step_wait_counters(Workspace &ws, hipStream_t st, FrameResult &fr, bo
     fr.n_surv = h->n_survivors;
     fr.n_newly = h->n_newly;
     fr.n_sel = h->n_selected;
+    fr.redo = h->redo != 0u;
     *overflow = fr.K > 0 && h->n_sorted == 0;
     if (*overflow && fr.K > kMaxKeys)
         return fail(TGS_ERR_CAPACITY, "frame needs " + std::to_string(fr.K) +
                                           " or more Gaussian-tile keys; the limit is " +
                                           std::to_string(kMaxKeys));
-    if (!*overflow) ws.last_K = fr.K;
+    if (!*overflow && !fr.redo) ws.last_K = fr.K;
     return TGS_OK;
 }
 
 // After an overflow: let the frame drain, then grow the key buffers.
 tgs_status grow_after_overflow(Workspace &ws, const FrameResult &fr, bool packed, hipStream_t st) {
     TGS_HIP(hipStreamSynchronize(st));
+    if (fr.redo) {   // the buffers are large enough, the depth order was not found
+        ws.radix_depth = true;
+        return TGS_OK;
+    }
     const size_t want = (size_t)fr.K + fr.K / 4 + 65536;
     return ws.ensure_keys(want, packed);
 }
@@ -541,7 +574,8 @@ tgs_status step_keys(const tgs_scene *sc, Workspace &ws, int TX, int TY, const u
     {
         ProfScope ps(TGS_PROF_DUPLICATE, st);
         launch_duplicate(n, cap, cnt, didx, ws.offs.as<uint32_t>(), ws.kfirst.as<uint32_t>(),
-                         ws.rect.as<ushort4>(), sat, sel_cols, TX, TX * TY, tp,
+                         ws.frame_samples ? depth_scratch(depth_plan(n, 1), n, ws.dsort.p).srect : ws.rect.as<ushort4>(),
+                         ws.frame_samples, sat, sel_cols, TX, TX * TY, tp,
                          ws.tkey.as<uint32_t>(), ws.tval.as<uint32_t>(), ws.ranges.as<uint2>(),
                          ws.tile_len.as<uint32_t>(),
                          counted ? sort_count_rows(ws.sort.as<uint32_t>()) : nullptr, st);
@@ -877,6 +911,7 @@ tgs_status tgs_render_full(tgs_scene *sc, const tgs_camera *cam, tgs_frame_out *
     const int W = cam->width, H = cam->height, TX = (W + 15) / 16, TY = (H + 15) / 16;
     Workspace &ws = sc->ws;
     TGS_TRY(ws.prepare(sc->n, W, H));
+    ws.radix_depth = false;
     const CamK ck = make_camk(cam);
     const bool packed = tile_sort_plan(sc->n, tile_id_bits(TX, TY)).packed;
     TGS_TRY(ws.ensure_keys(ws.key_cap ? ws.key_cap : 4 * (size_t)sc->n + 65536, packed));
@@ -905,8 +940,8 @@ tgs_status tgs_render_full(tgs_scene *sc, const tgs_camera *cam, tgs_frame_out *
         }
         bool overflow = false;
         TGS_TRY(step_wait_counters(ws, st, fr, &overflow));
-        ws.recent_K[0] = fr.K;
-        if (!overflow) break;
+        if (!fr.redo) ws.recent_K[0] = fr.K;
+        if (!overflow && !fr.redo) break;
         TGS_TRY(grow_after_overflow(ws, fr, packed, st));
     }
     sc->last_W = W;
@@ -979,8 +1014,10 @@ struct Carve {
 // Lays the workspace of a full render (n Gaussians, W x H, key_cap keys) over
 // [base, base + cap), with packed keys or with (tile id, index) words; false
 // if it does not fit.  The words' layout sets the capacity of a size; packed
-// keys take less of the array, except for the count rows of very few keys.
-bool layout_full(Workspace &ws, char *base, size_t cap, int n, int W, int H, size_t key_cap, bool packed) {
+// keys take less of the array, except for the count rows of very few keys,
+// and (samples) the sample sort by depth takes what they leave.
+bool layout_full(Workspace &ws, char *base, size_t cap, int n, int W, int H, size_t key_cap, bool packed,
+                 bool samples = false) {
     Carve c{base, cap, 0};
     const size_t nn = (size_t)(n > 0 ? n : 1);
     const int TX = (W + 15) / 16, TY = (H + 15) / 16;
@@ -1002,6 +1039,7 @@ bool layout_full(Workspace &ws, char *base, size_t cap, int n, int W, int H, siz
               (packed ? c.take(ws.segments, tile_sort_segment_words((uint32_t)key_cap) * 4) &&
                             c.take(ws.tile_len, nt * 4)
                       : c.take(ws.tkey_alt, key_cap * 4)) &&
+              (!samples || c.take(ws.dsort, depth_plan(n, 1).words * 8)) &&
               c.take(ws.tval_alt, key_cap * 4) &&
               c.take(ws.kfirst, key_blocks(key_cap) * sizeof(uint32_t));
     void *hc = ok ? c.raw(sizeof(HostCounters)) : nullptr;
@@ -1053,37 +1091,43 @@ tgs_status tgs_render_full_noalloc(const tgs_scene *sc, const tgs_camera *cam, t
         else hi = mid - 1;
     }
     const bool packed = tile_sort_plan(sc->n, tile_id_bits(TX, TY)).packed;
-    if (!(packed && layout_full(ws, base, kNoAllocBytes, sc->n, W, H, lo, true)) &&
-        !layout_full(ws, base, kNoAllocBytes, sc->n, W, H, lo, false))
-        return fail(TGS_ERR_DEVICE, "scratch layout failed");
+    if (!(packed && depth_plan(sc->n, 1).ok && layout_full(ws, base, kNoAllocBytes, sc->n, W, H, lo, true, true))) {
+        ws.dsort.p = nullptr;
+        if (!(packed && layout_full(ws, base, kNoAllocBytes, sc->n, W, H, lo, true)) &&
+            !layout_full(ws, base, kNoAllocBytes, sc->n, W, H, lo, false))
+            return fail(TGS_ERR_DEVICE, "scratch layout failed");
+    }
     // no profiling events in this call (creating one allocates)
     struct NoAllocScope {
         NoAllocScope() { t_no_alloc = true; }
         ~NoAllocScope() { t_no_alloc = false; }
     } scope;
-    // the counters read back must start clear: the array keeps the last
-    // call's contents
-    launch_fill_u8(reinterpret_cast<uint8_t *>(ws.host_cnt_dev), sizeof(HostCounters), 0, st);
-    TGS_LAUNCHED("clear counters");
     const CamK ck = make_camk(cam);
-    TGS_TRY(step_preprocess(sc, ws, ck, no_cull(0.2f, ws), st));
-    const uint32_t *didx = nullptr, *vals = nullptr;
-    TGS_TRY(step_scan(sc, ws, nullptr, TX, st, &didx));
-    TGS_TRY(step_keys(sc, ws, TX, TY, nullptr, nullptr, didx, st, &vals));
-    if (out->contrib) launch_fill_f32(out->contrib, (size_t)sc->n, 0.0f, st);
-    BlendArgs a = blend_args(ws, cam, vals);
-    set_blend_order(a, ws, sc);
-    a.rgb = out->rgb;
-    a.depth = out->depth;
-    a.sigma = out->sigma;
-    a.alpha = out->alpha;
-    a.contrib = out->contrib;
-    a.mark_mask = out->tile_mask;
-    launch_blend(a, TX * TY, st, nullptr, nullptr);
-    TGS_LAUNCHED("blend");
     FrameResult fr;
     bool overflow = false;
-    TGS_TRY(step_wait_counters(ws, st, fr, &overflow));
+    do {
+        ws.radix_depth = fr.redo;   // (a second time round: with the radix passes)
+        // the counters read back must start clear: the array keeps the last
+        // call's contents
+        launch_fill_u8(reinterpret_cast<uint8_t *>(ws.host_cnt_dev), sizeof(HostCounters), 0, st);
+        TGS_LAUNCHED("clear counters");
+        TGS_TRY(step_preprocess(sc, ws, ck, no_cull(0.2f, ws), st));
+        const uint32_t *didx = nullptr, *vals = nullptr;
+        TGS_TRY(step_scan(sc, ws, nullptr, TX, st, &didx));
+        TGS_TRY(step_keys(sc, ws, TX, TY, nullptr, nullptr, didx, st, &vals));
+        if (out->contrib) launch_fill_f32(out->contrib, (size_t)sc->n, 0.0f, st);
+        BlendArgs a = blend_args(ws, cam, vals);
+        set_blend_order(a, ws, sc);
+        a.rgb = out->rgb;
+        a.depth = out->depth;
+        a.sigma = out->sigma;
+        a.alpha = out->alpha;
+        a.contrib = out->contrib;
+        a.mark_mask = out->tile_mask;
+        launch_blend(a, TX * TY, st, nullptr, nullptr);
+        TGS_LAUNCHED("blend");
+        TGS_TRY(step_wait_counters(ws, st, fr, &overflow));
+    } while (fr.redo);
     if (overflow)
         return fail(TGS_ERR_CAPACITY, "frame needs " + std::to_string(fr.K) +
                                           " Gaussian-tile keys; the allocation-free render holds " +
@@ -1163,6 +1207,7 @@ tgs_status tgs_render_temporal(tgs_state *s, const tgs_camera *cam, tgs_frame_ou
     const int W = s->W, H = s->H, TX = s->TX, TY = s->TY, nt = TX * TY;
     Workspace &ws = s->ws;
     TGS_TRY(ws.prepare(sc->n, W, H));
+    ws.radix_depth = false;
     const CamK ck = make_camk(cam);
     const tgs_params &p = s->p;
 
@@ -1335,8 +1380,8 @@ tgs_status tgs_render_temporal(tgs_state *s, const tgs_camera *cam, tgs_frame_ou
         }
         bool overflow = false;
         TGS_TRY(step_wait_counters(ws, st, fr, &overflow));
-        ws.recent_K[kind == TGS_FRAME_TGS ? 1 : 0] = fr.K;
-        if (!overflow) break;
+        if (!fr.redo) ws.recent_K[kind == TGS_FRAME_TGS ? 1 : 0] = fr.K;
+        if (!overflow && !fr.redo) break;
         TGS_TRY(grow_after_overflow(ws, fr, packed, st));
     }
     if (kind != TGS_FRAME_TGS) {

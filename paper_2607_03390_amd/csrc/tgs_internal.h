@@ -55,9 +55,22 @@ struct Records {
     ushort4 *rect;            // tile rectangle x0, y0, x1, y1 (x0 > x1: empty)
     uint8_t *status;          // bit0 survivor, bit1 newly visible
     uint32_t *count;          // keys of the Gaussian (tiles of its rectangle)
-    uint32_t *dkey;           // float bits of the depth (depth-sort key)
+    uint32_t *dkey;           // float bits of the depth (depth-sort key); kNoDepth: no keys
     uint32_t *partial;        // per 256-Gaussian block: survivors, newly visible
+    // optional: the depth keys of one Gaussian per stratum of sample_stride,
+    // for the depth order's splitters (sample_magic = ceil(2^40 / stride):
+    // i * magic >> 40 is i / stride for i < 2^23)
+    uint32_t *samples;
+    uint32_t sample_stride;
+    uint64_t sample_magic;
 };
+constexpr uint32_t kNoDepth = 0xffffffffu;
+// The sampled Gaussian of stratum q (`stride` consecutive ones): at a place
+// hashed from its number, so that no order of the scene is met in step.
+__host__ __device__ inline uint32_t depth_sample_at(uint32_t q, uint32_t stride, int n) {
+    const uint32_t at = q * stride + (uint32_t)((uint64_t)(q * 0x9e3779b1u) * stride >> 32);
+    return at < (uint32_t)(n - 1) ? at : (uint32_t)(n - 1);
+}
 
 // Temporal dynamic culling inputs of the preprocess.
 struct CullK {
@@ -92,19 +105,21 @@ struct Counters {
 // a copy.
 struct HostCounters {
     uint32_t n_keys, n_survivors, n_newly, n_selected, n_visible, n_sorted;
-    uint32_t pad;
+    uint32_t redo;   // 1: the frame has no keys and is to be rendered again (a bucket of the
+                     // sample sort overflowed) with the radix passes
     uint32_t tag;
 };
 
-// Writes the frame's counters to the host: the six values as two vector
+// Writes the frame's counters to the host: the seven values as vector
 // stores, a system-scope fence (they are complete and visible), then the tag
 // as a relaxed store that nothing waits for.  (A volatile store would wait
 // for its own round trip to host memory, one after another.)
 __device__ inline void publish_host(HostCounters *h, uint32_t n_keys, uint32_t n_survivors,
                                     uint32_t n_newly, uint32_t n_selected, uint32_t n_visible,
-                                    uint32_t n_sorted, uint32_t tag) {
+                                    uint32_t n_sorted, uint32_t redo, uint32_t tag) {
     reinterpret_cast<uint4 *>(h)[0] = make_uint4(n_keys, n_survivors, n_newly, n_selected);
     reinterpret_cast<uint2 *>(h)[2] = make_uint2(n_visible, n_sorted);
+    h->redo = redo;
     __threadfence_system();
     __hip_atomic_store(&h->tag, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
@@ -163,6 +178,7 @@ __device__ inline void mark_key_blocks(uint32_t *kfirst, uint32_t nb, uint32_t s
 // (cap bounds n_sorted for the grid; nothing is emitted past the key
 // capacity) and clears the tile ranges and lengths (filled by the tile sort, or
 // the ranges by launch_ranges after it).  sat / sel_cols are NULL in frames that render every tile.
+// rect: by Gaussian index, or (rect_sorted) in the order of didx.
 // Keys: tile id to tkey and index to tval, or (tp.packed) the low digit bytes
 // to tkey and the payload to tval (launch_tile_sort).  rows (optional): per
 // block of kKeyBlock keys, the counts of the low digit in row b of
@@ -170,7 +186,7 @@ __device__ inline void mark_key_blocks(uint32_t *kfirst, uint32_t nb, uint32_t s
 struct TileSortPlan;
 void launch_duplicate(int n, uint32_t cap, const Counters *cnt, const uint32_t *didx,
                       const uint32_t *offs, const uint32_t *kfirst, const ushort4 *rect,
-                      const uint32_t *sat, const int *sel_cols, int TX, int n_tiles,
+                      bool rect_sorted, const uint32_t *sat, const int *sel_cols, int TX, int n_tiles,
                       const TileSortPlan &tp, uint32_t *tkey, uint32_t *tval, uint2 *ranges,
                       uint32_t *tile_len, uint32_t *rows, hipStream_t st);
 // Ranges of the cnt->n_sorted tile-sorted keys; cap bounds n_sorted for the grid.
@@ -271,6 +287,34 @@ void launch_depth_sort(int n, uint32_t *count, const ushort4 *rect, const uint32
                        uint32_t *v_b, uint32_t *offs, uint32_t *kfirst, uint32_t *scratch,
                        Counters *cnt, uint32_t cap, const uint32_t *pre_partial, int n_pre,
                        HostCounters *host, uint32_t tag, hipStream_t st);
+
+// ---- launchers (k_depthsort.hip) ----
+// Depth order of the Gaussians that have keys by a sample sort: sizes for a
+// scene of n Gaussians on a grid of n_tiles (ok: taken at all), the parts of its scratch (words
+// 8-byte words) and the sort, with the outputs of launch_depth_sort and the
+// sorted Gaussians' rectangles (DepthScratch::srect).  Without keys to
+// publish, because a bucket overflowed: HostCounters::redo.
+struct DepthPlan {
+    bool ok;
+    int stride, ns;     // samples: one per stride Gaussians
+    int nb, log_nb;     // buckets
+    uint32_t cap;       // entries of a bucket's region
+    size_t words;
+};
+struct DepthScratch {
+    uint4 *entries;
+    uint64_t *splitters, *fill;
+    ushort4 *srect;
+    uint32_t *samples;
+};
+constexpr int kDepthSamples = 16384;   // at most
+DepthPlan depth_plan(int n, int n_tiles);
+DepthScratch depth_scratch(const DepthPlan &dp, int n, void *base);
+void launch_depth_samplesort(const DepthPlan &dp, const DepthScratch &d, int n, const uint32_t *dkey,
+                             const ushort4 *rect, const uint32_t *sat, int TX, uint32_t *didx,
+                             uint32_t *offs, uint32_t *kfirst, Counters *cnt, uint32_t cap,
+                             const uint32_t *pre_partial, int n_pre, HostCounters *host, uint32_t tag,
+                             hipStream_t st);
 
 // ---- launchers (k_segsort.hip) ----
 // Per-tile depth order without the global depth sort: key counts scanned in

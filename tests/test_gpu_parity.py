@@ -291,6 +291,57 @@ def test_tile_sort_grid_edges(W, H, n):
     _full_parity(sc, cams, sample_tiles=sample, label=f"tile sort {TX}x{TY}")
 
 
+def _depth_samples(n):
+    """Indices of the Gaussians whose depths the sample sort takes splitters
+    from: one per stratum of ceil(n / 4096) (scenes of up to 524288)."""
+    stride = -(-n // 4096)
+    q = np.arange(-(-n // stride), dtype=np.uint64)
+    at = q * stride + ((q * 0x9e3779b1 & 0xffffffff) * stride >> 32)
+    return np.minimum(at, n - 1).astype(np.int64)
+
+
+# the smallest scenes (a stratum per Gaussian), one past whole strata, and all
+# Gaussians at one depth (split by index)
+@pytest.mark.parametrize("n,flat", [(1, False), (15, False), (17, False), (4097, False), (9001, False),
+                                    (9001, True)])
+def test_depth_order_scene_sizes(n, flat):
+    """Depth order at the edges of the sample sort's sizes: lists bit-exact."""
+    sc = synth.small_scene(n, 23, degree=0)
+    if flat:
+        sc.means[:, 1] = 0.0
+    cams = [synth.make_camera(synth.look_at((0.0, -3.0, 0.0), (0, 0, 0)), 130, 70)]
+    _full_parity(sc, cams, label=f"depth order n {n} flat {flat}")
+
+
+def test_depth_order_bucket_overflow():
+    """A scene whose sampled Gaussians say nothing of the others' depths (those
+    lie between two samples): a bucket overflows and the frame is rendered
+    again by the radix passes, in full, temporal and allocation-free calls."""
+    import torch
+    n = 20_000
+    sc = synth.small_scene(n, 29, degree=0)
+    sampled = np.zeros(n, bool)
+    sampled[_depth_samples(n)] = True
+    assert 3000 < sampled.sum() < 5000
+    rng = np.random.default_rng(3)
+    sc.means[sampled, 1] = rng.uniform(-1.0, 1.0, sampled.sum())
+    sc.means[~sampled, 1] = rng.uniform(0.0, 1e-4, (~sampled).sum())
+    cams = synth.orbit_path(3, 4.0, 0.0, 0.0, 200, 120)
+    _full_parity(sc, cams[:1], label="bucket overflow")
+    _temporal_parity(sc, cams, 200, 120, "bucket overflow")
+    with Uploaded(sc) as h:
+        tgs.tgs_profile_start()
+        want = gpu_full(h, cams[0], n)
+        frames = tgs.tgs_profile_stop()["preprocess"]["launches"]
+        assert frames == (2 if SETTINGS["sort"] == tgs.SORT_DEPTH_FIRST else 1), frames
+        out = tgs.alloc_frame(200, 120, n, depth=True, contrib=True, tile_mask=True)
+        info = tgs.tgs_render_full_noalloc(h, cams[0], **out)
+        torch.cuda.synchronize()
+        assert info["n_keys"] == want["n_keys"]
+        for k, v in out.items():
+            assert np.array_equal(v.cpu().numpy(), want[k]), k
+
+
 def test_full_parity_object_subset():
     w = synth.workload("object", n_gaussians=40_000)
     _full_parity(w.scene, [w.cameras[0], w.cameras[37]], label="object 40k")

@@ -313,6 +313,23 @@ def test_depth_order_scene_sizes(n, flat):
     _full_parity(sc, cams, label=f"depth order n {n} flat {flat}")
 
 
+# three planes head-on with a few Gaussians between them: buckets of entries
+# crowded into one or two depths, of one power of two and past it
+@pytest.mark.parametrize("n", [4096, 9001, 60_000])
+def test_depth_order_crowded_depths(n):
+    """Depth order where a bucket holds many Gaussians of few depths (and its
+    sub-buckets are crowded): lists bit-exact."""
+    sc = synth.small_scene(n, 31, degree=0, log_scale_mean=-4.0)
+    rng = np.random.default_rng(5)
+    plane = rng.integers(0, 3, n)
+    # planes at uneven distances; one Gaussian in fifty off its plane
+    sc.means[:, 1] = np.array([-0.5, -0.4999, 0.6], np.float32)[plane]
+    off = rng.random(n) < 0.02
+    sc.means[off, 1] = rng.uniform(-1.0, 1.0, off.sum())
+    cams = [synth.make_camera(synth.look_at((0.0, -3.0, 0.0), (0, 0, 0)), 130, 70)]
+    _full_parity(sc, cams, label=f"crowded depths n {n}")
+
+
 def test_depth_order_bucket_overflow():
     """A scene whose sampled Gaussians say nothing of the others' depths (those
     lie between two samples): a bucket overflows and the frame is rendered

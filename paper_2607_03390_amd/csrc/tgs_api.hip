@@ -173,6 +173,9 @@ struct Workspace {
     tgs_status ensure_keys(size_t want, bool packed) {
         if (want > (size_t)kMaxKeys) want = kMaxKeys;
         if (want < key_cap) want = key_cap;
+        // the last frame's lists end here: its tile ranges are about to be
+        // cleared, and a frame that fails leaves no lists to dump
+        last_K = 0;
         // (a buffer that is large enough stays as it is)
         TGS_TRY(tkey.ensure(packed ? want + 16 : want * sizeof(uint32_t)));
         TGS_TRY(tval.ensure(want * sizeof(uint32_t)));

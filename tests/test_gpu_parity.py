@@ -383,6 +383,31 @@ def test_key_capacity_growth():
     assert st["frames"] == 3
 
 
+def test_dump_after_a_refused_frame():
+    """A frame of more keys than the library takes (4.6e9) is refused; its tile
+    ranges are empty, and so are the sorted keys and values dumped after it
+    (not the earlier frame's, whose ranges are gone)."""
+    n = 70_000
+    sc = synth.small_scene(n, 3, degree=0, log_scale_mean=2.5)
+    far, near = (synth.make_camera(synth.look_at((0.0, -d, 0.0), (0, 0, 0)), 4096, 4096) for d in (6e4, 30.0))
+    near_keys = int(O.tile_counts(O.gaussians(sc, near), *near.tiles)[-1])
+    assert near_keys > 0xffff0000, near_keys
+    out = tgs.alloc_frame(4096, 4096)
+    with Uploaded(sc) as h:
+        info = tgs.tgs_render_full(h, far, **out)
+        assert tgs.tgs_debug_dump(h, None, tgs.TGS_DUMP_SORTED_KEYS).size == info["n_keys"] > 0
+        with pytest.raises(tgs.TgsError) as e:
+            tgs.tgs_render_full(h, near, **out)
+        assert e.value.status == tgs.TGS_ERR_CAPACITY
+        ranges = tgs.tgs_debug_dump(h, None, tgs.TGS_DUMP_TILE_RANGES)
+        keys = tgs.tgs_debug_dump(h, None, tgs.TGS_DUMP_SORTED_KEYS)
+        vals = tgs.tgs_debug_dump(h, None, tgs.TGS_DUMP_SORTED_VALUES)
+        assert not ranges.any() and keys.size == 0 and vals.size == 0
+        # and the next frame's are its own
+        info = tgs.tgs_render_full(h, far, **out)
+        assert tgs.tgs_debug_dump(h, None, tgs.TGS_DUMP_SORTED_KEYS).size == info["n_keys"]
+
+
 def test_empty_and_invisible_scenes():
     import torch
     sc = synth.small_scene(0, 0, degree=0)

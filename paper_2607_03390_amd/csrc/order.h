@@ -17,21 +17,31 @@ namespace tgs {
 // Bucket of a list length: floor(log2(len)) + 1, 0 for an empty list.
 __device__ inline uint32_t length_bucket(uint32_t len) { return len ? 32u - (uint32_t)__clz(len) : 0u; }
 
-// Length bucket from which a frame of n_keys keys splits its tiles, at most
-// most: lists of at least the keys that 1024 evenly loaded blocks would each
-// hold, rounded up to a power of two, but no shorter than 32.  A list longer
+// Length bucket from which a frame of n_keys keys on n_tiles tiles to render
+// splits its tiles, at most most: lists of at least the keys that 1024 evenly
+// loaded blocks would each hold, rounded up to a power of two.  A list longer
 // than that is still walked when the rest of the chip has run dry (about
 // 2048 tile blocks are resident at once), so its tile sets the launch's tail
 // and four quadrant blocks shorten it; shorter ones are only staged four
-// times for nothing.  Measured at thresholds of 2^5 .. 2^13 (blend launch,
-// microseconds): 34k keys on 256 tiles 17.4 up to 2^8, 24.4 from 2^9;
-// 107k keys on 920 tiles with every output 107 up to 2^9, 110 at 2^10, 251
-// at 2^12; 731k keys on 3600 tiles 66 at 2^5, 60.9 at 2^10, 104 at 2^12;
-// 562k - 1.1M keys on the selected tiles of a room 72 up to 2^8, 58.8 from
-// 2^10; 5.0M keys on 8160 tiles 112 at 2^5, 105 from 2^9.
-__device__ inline int split_bucket_for(uint32_t n_keys, int most) {
+// times for nothing.  Frames with few keys have a lower bound besides: 32
+// where all tiles' quadrants are resident at once (512 tiles), and more on
+// larger grids, where quadrants of short lists are only more blocks to
+// launch.  Measured at thresholds of 2^5 .. 2^13 (blend launch, microseconds),
+// by the keys: 107k keys on 920 tiles with every output 54 up to 2^9, 88 at
+// 2^10, 149 at 2^12; 745k keys on 3600 tiles 59 up to 2^8, 69 at 2^10, 88 at
+// 2^12; 572k - 1.1M keys on the selected tiles of a room 72 up to 2^9, 58
+// from 2^10; 5.0M keys on 8160 tiles 101 - 110 at all.  By the grid: 34k
+// keys on 256 tiles 12 up to 2^7, 16 at 2^8, 22 from 2^9; 12k on 468 tiles 8.8
+// at 2^6, 9.8 at 2^7; 38k on 920 tiles 11.8 at 2^6, 14.6 at 2^7; 53k on 1600
+// tiles 15.0 at 2^6, 13.1 from 2^7; 72k on 3600 tiles 17.6 at 2^6, 16.1 at
+// 2^7, 18.3 at 2^8; 96k on 6300 tiles 17.3 at 2^7, 16.3 at 2^8.  (Of wide
+// opaque Gaussians few entries of a list are walked before the pixels stop,
+// and splitting at all costs up to a tenth: 532k keys on 3600 tiles 27.5 at
+// 2^12, 29.7 at 2^10, 35 at 2^8.  The lengths do not tell.)
+__device__ inline int split_bucket_for(uint32_t n_keys, int n_tiles, int most) {
     const uint32_t mean = n_keys >> 10;
-    const int lg = mean > 32u ? 32 - __clz(mean - 1u) : 5;
+    const int least = 5 + (n_tiles > 512) + (n_tiles > 1024) + (n_tiles > 4096);
+    const int lg = mean > 1u << least ? 32 - __clz(mean - 1u) : least;
     return lg + 1 < most ? lg + 1 : most;
 }
 
@@ -68,9 +78,10 @@ __device__ inline void wave_bucket_rank(uint32_t *wc, const uint32_t (&b)[N], co
 }
 
 // First place of bucket 32 - tid in the order (buckets longest first) from
-// its tiles c; with `publish` also the split count and, for the host, the
-// longest bucket.  Run by one whole wave (tid < 64; c = 0 from tid 33 on).
-__device__ inline uint32_t order_bucket_start(const OrderK &o, uint32_t c, bool publish) {
+// its tiles c (of n in all); with `publish` also the split count and, for the
+// host, the longest bucket.  Run by one whole wave (tid < 64; c = 0 from tid
+// 33 on).
+__device__ inline uint32_t order_bucket_start(const OrderK &o, uint32_t c, int n, bool publish) {
     const int tid = threadIdx.x, b = 32 - tid;
     uint32_t inc = c;
 #pragma unroll
@@ -82,7 +93,7 @@ __device__ inline uint32_t order_bucket_start(const OrderK &o, uint32_t c, bool 
     // the tiles the blend splits, a prefix of the order: those of the
     // buckets from the lowest one >= split_bucket that leaves at most
     // max_split tiles in it and above (whole buckets)
-    const int sb = o.n_keys && o.split_bucket >= 1 ? split_bucket_for(*o.n_keys, o.split_bucket)
+    const int sb = o.n_keys && o.split_bucket >= 1 ? split_bucket_for(*o.n_keys, n, o.split_bucket)
                                                    : o.split_bucket;
     const uint64_t fit = __ballot(sb >= 1 && b >= sb && inc <= (uint32_t)o.max_split);
     const uint32_t ns = __shfl(inc, fit ? 63 - __clzll((long long)fit) : 0);
@@ -138,7 +149,7 @@ __device__ void order_tiles_share(const OrderK &o, int n, int share, int n_share
                 ca += after[w * kOrderBuckets + 32 - tid];
             }
         }
-        const uint32_t start = order_bucket_start(o, cb + ca, share == 0);
+        const uint32_t start = order_bucket_start(o, cb + ca, n, share == 0);
         if (tid <= 32) before[32 - tid] = start + cb;
     }
     __syncthreads();

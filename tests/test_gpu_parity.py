@@ -188,9 +188,11 @@ def split_auto():
 
 
 # fewer than 32 keys per 1024 (threshold 32), a threshold between the two
-# bounds, and one past the most tiles that are split
+# bounds, and one past the most tiles that are split; then the lower bounds of
+# larger grids (1600 and 4600 tiles)
 @pytest.mark.parametrize("n,log_scale,W,H", [(700, -3.0, 200, 136), (24_000, -2.6, 48, 40),
-                                             (20_000, -4.0, 641, 359)])
+                                             (20_000, -4.0, 641, 359), (6_000, -3.0, 800, 500),
+                                             (6_000, -3.0, 1472, 800)])
 def test_split_auto_full_parity(split_auto, n, log_scale, W, H):
     """Tiles split from the frame's own threshold: images, moments and the
     Gaussian buffer against the oracle."""

@@ -293,20 +293,18 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(int TX, int TY, int
             if (mode) {
                 part = grp == 0 ? (uint32_t)ty : 0u;
             } else {
-                int y = grp;
-                for (; y + 7 * groups < ty; y += 8 * groups) {
+                // clamped rows, no branches: each round's loads are in flight
+                // together
+                for (int y0 = grp; y0 < ty; y0 += 8 * groups) {
                     uint32_t f[8];
 #pragma unroll
                     for (int k = 0; k < 8; ++k) {
-                        const size_t t = (size_t)(y + k * groups) * TX + x;
+                        const int y = y0 + k * groups;
+                        const size_t t = (size_t)(y < ty ? y : y0) * TX + x;
                         f[k] = (uint32_t)(oc[t] | um[t]);
                     }
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) part += f[k];
-                }
-                for (; y < ty; y += groups) {
-                    const size_t t = (size_t)y * TX + x;
-                    part += (uint32_t)(oc[t] | um[t]);
+                    for (int k = 0; k < 8; ++k) part += y0 + k * groups < ty ? f[k] : 0u;
                 }
             }
         }

@@ -329,9 +329,11 @@ tgs_status tgs_profile_stop(tgs_profile *out);
  *     sorts its list by (depth bits, index) in LDS (lists above 4096 entries
  *     take a slower in-block path);
  *   TGS_SORT_AUTO (default): per frame, the per-tile sort for scenes with
- *     fewer than 8192 Gaussians (and for TemporalGS frames above 2^23), when
- *     the longest tile list of a recent frame of the same kind has fewer than
- *     4096 entries; else the depth-first sort.
+ *     fewer than 8192 Gaussians, for scenes with fewer than 24576 when a
+ *     recent frame of the same kind had fewer than 24 keys per tile, and for
+ *     TemporalGS frames where the sample sort does not reach, when the longest
+ *     tile list of a recent frame of the same kind has fewer than 4096
+ *     entries; else the depth-first sort.
  * INVALID_ARG for a NULL scene or another value.  Like every call on a
  * scene, it must not overlap with renders through it. */
 enum { TGS_SORT_AUTO = 0, TGS_SORT_DEPTH_FIRST = 1, TGS_SORT_PER_TILE = 2 };

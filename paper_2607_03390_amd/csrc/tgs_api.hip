@@ -365,9 +365,7 @@ struct ProfScope {
 struct tgs_scene {
     int n = 0, deg = 0, ncoef = 1;
     int tile_bound = TGS_TILES_3SIGMA;
-    // how each tile's depth order is produced: 0 = per frame (the per-tile
-    // sort in selective-rendering frames when the longest tile list of a
-    // recent frame fits its LDS bound, else the global depth sort), 1 =
+    // how each tile's depth order is produced: 0 = per frame (step_scan), 1 =
     // always the global depth sort, 2 = always the per-tile sort
     int sort_path = TGS_SORT_AUTO;
     // list length bucket from which the blend splits tiles into quadrants
@@ -429,11 +427,20 @@ tgs_status step_preprocess(const tgs_scene *sc, Workspace &ws, const CamK &cam, 
     return TGS_OK;
 }
 
-// Scenes below this many Gaussians sort each tile's list instead of the
-// Gaussians by depth where the lists are short: one launch fewer.  (Full
-// render, per-tile and by depth: 2k Gaussians 41.6 and 43.6 us, 10k 49.3 and
-// 48.8, 60k 163 and 142, 130k 129 and 104; temporal interval of 1.5M 1928 and
-// 1755 us.)
+// Scenes below kSegSmallScene Gaussians sort each tile's list instead of the
+// Gaussians by depth where the lists are short: one launch fewer.  Up to
+// kSegSparseScene they do where the keys of a recent frame of the same kind
+// were at most kSegSparseKeys a tile: then a block per tile has next to
+// nothing to sort, while the sample sort still ranks and scatters every
+// Gaussian.  (Full render / frame of a temporal sequence, us, per-tile and by
+// depth, by Gaussians and keys a tile: 5k, 5: 54.4 / 65.4 and 57.1 / 68.8; 9k,
+// 10: 53.5 / 65.5 and 56.9 / 69.1; 16k, 9: 56.8 / 68.7 and 60.2 / 71.1; 16k,
+// 18: 57.7 / 68.4 and 59.1 / 71.7; 30k, 17: 60.3 / 72.3 and 60.4 / 72.4; 16k,
+// 33: 59.3 / 70.3 and 58.8 / 70.0; 9k, 60: 63.2 / 73.8 and 61.9 / 72.2; 60k,
+// 66: 71.9 / 85.9 and 71.0 / 84.5; 120k, 200: 123.5 / 136.6 and 103.1 / 116.0;
+// temporal interval of 1.5M 1928 and 1755 us.)
+constexpr int kSegSparseScene = 24576;
+constexpr uint32_t kSegSparseKeys = 24;
 constexpr int kSegSmallScene = 8192;
 
 // The Gaussians that have keys and the start of their keys, in the order the
@@ -443,12 +450,15 @@ constexpr int kSegSmallScene = 8192;
 tgs_status step_scan(const tgs_scene *sc, Workspace &ws, const uint32_t *sat, int TX,
                      hipStream_t st, const uint32_t **sorted_didx) {
     const int n = sc->n;
-    // per frame: the per-tile sort in small scenes, and, where the sample
-    // sort by depth does not reach (2^23 Gaussians), in selective-rendering
-    // frames, whose keys are few beside the Gaussians; in both where a recent
+    // per frame: the per-tile sort in small and sparse scenes, and, where the
+    // sample sort by depth does not reach (2^23 Gaussians), in selective-rendering
+    // frames, whose keys are few beside the Gaussians; in all where a recent
     // frame's lists fit the per-tile sort's LDS bound
-    const DepthPlan dp = depth_plan(n, TX * ((ws.H + 15) / 16));
-    const bool prefer_seg = dp.ok ? n < kSegSmallScene : sat != nullptr;
+    const int nt = TX * ((ws.H + 15) / 16);
+    const DepthPlan dp = depth_plan(n, nt);
+    const uint32_t recent = ws.recent_K[sat ? 1 : 0];
+    const bool sparse = n < kSegSparseScene && recent != kUnknownKeys && recent / kSegSparseKeys < (uint32_t)nt;
+    const bool prefer_seg = dp.ok ? n < kSegSmallScene || sparse : sat != nullptr;
     const uint32_t maxb = ws.host_maxb ? reinterpret_cast<volatile uint32_t *>(ws.host_maxb)[sat ? 1 : 0]
                                        : 0xffffffffu;
     ws.frame_samples = false;

@@ -1,12 +1,14 @@
 // Depth order of the Gaussians that have keys (Sec. III-A), by a sample sort
-// in three launches, for scenes of up to 2^23 Gaussians (k_sort.hip's radix
-// passes otherwise, and when a bucket overflows):
+// in three launches, for scenes of fewer than 2^23 Gaussians and 2^40
+// (Gaussian, tile) pairs (k_sort.hip's radix passes otherwise, and when a
+// bucket overflows):
 //
-//  1. The preprocess leaves one sample per stratum of consecutive Gaussians: the depth bits of a Gaussian at a hashed place (kNoDepth: it
-//     has no keys).  The splitter kernel ranks every valid sample against all
-//     the others and takes one in sixteen as a splitter (depth bits, index):
-//     with the index, equal depths (a wall seen head-on) are split as evenly
-//     as any others.
+//  1. The preprocess leaves one sample per stratum of consecutive Gaussians:
+//     the depth bits of a Gaussian at a hashed place (kNoDepth: it has no
+//     keys).  The splitter kernel ranks every valid sample against all the
+//     others and takes one in sixteen (of 2048 buckets: one in eight) as a
+//     splitter (depth bits, index): with the index, equal depths (a wall seen
+//     head-on) are split as evenly as any others.
 //  2. The scatter kernel finds each Gaussian's bucket by bisection of the
 //     splitters in LDS, counts its block's Gaussians and keys per bucket
 //     there, reserves places in the buckets' regions with one add per (block,
@@ -19,10 +21,10 @@
 //     frame's counters.
 //
 // The order of arrival in a bucket depends on timing, its sorted order does
-// not.  A bucket beyond its region (2.7 times the mean spacing of sixteen
-// samples where every Gaussian of the largest scenes is visible: about 1e-6;
-// 4 times or more elsewhere) makes the frame publish no keys and
-// HostCounters::redo, and the host renders it again with the radix passes.
+// not.  A bucket beyond its region (depth_plan.h: below one frame in a
+// thousand where depths know nothing of the order of the scene) makes the
+// frame publish no keys and HostCounters::redo, and the host renders it again
+// by another way.
 //
 // Against twelve launches of radix passes (count, column scan, scatter, four
 // times), each latency-bound: 1.13M of 1.5M Gaussians 98 -> 66 us, 300k 62 -> 27
@@ -38,21 +40,18 @@ namespace {
 constexpr int kRankThreads = 512;
 constexpr int kRankBlocks = 256;      // of the splitter kernel, at most: one per CU
 constexpr int kScatterThreads = 512;
-constexpr int kBucketMost = 16384;    // entries of a bucket's region, at most
-constexpr int kBucketSmall = 4096;    // buckets sorted by 512-thread blocks, three to a CU
 constexpr int kBucketShort = 8192;    // buckets sorted with half the LDS of the longest
 
 // Members of a sub-bucket up to which it is ranked by compares: a compare per
 // member for each entry; beyond, the whole bucket is sorted by exchanges.
 constexpr uint32_t kCrowd = 128;
 
-// A bucket's fill and keys in one word: Gaussians in the low 23 bits, keys
+// A bucket's fill and keys in one word: Gaussians in the low kFillBits, keys
 // above (scenes of under 2^23 Gaussians and 2^40 (Gaussian, tile) pairs).
-constexpr int kFillBits = 24;
 __device__ inline uint32_t fill_of(uint64_t v) { return (uint32_t)v & ((1u << kFillBits) - 1u); }
 
 // Ranks the valid samples (depth bits, by stratum, that is by index) against
-// each other and writes every sixteenth as a splitter: thread (g, l) holds PER
+// each other and writes one per bucket, evenly spaced, as a splitter: thread (g, l) holds PER
 // of the block's 4 PER samples (g = tid & 3) and compares them with every
 // 128th of all (l = tid >> 2), one LDS read and PER compares at a time.  Samples
 // of equal depth rank by stratum: those before the block's count as lower
@@ -572,29 +571,6 @@ void scatter(const DepthPlan &dp, int n, const uint32_t *dkey, const ushort4 *re
 
 }  // namespace
 
-DepthPlan depth_plan(int n, int n_tiles) {
-    DepthPlan p{};
-    if (n < 1 || n >= 1 << 23 || (uint64_t)n * (uint64_t)n_tiles >= 1ull << (64 - kFillBits)) return p;
-    p.ok = true;
-    // A bucket per CU while they hold up to 6144 Gaussians each (of whom half
-    // to three quarters are usually visible), more buckets above: the fewer
-    // they are, the longer the runs of a block's entries in one region and
-    // the fewer samples have to be ranked.  Up to 16 samples per bucket, up
-    // to kDepthSamples; regions of four times a bucket's share of the
-    // Gaussians, as far as the LDS holds them.
-    const int want = n <= 256 * 6144 ? 256 : n <= 512 * 6144 ? 512 : 1024;
-    p.stride = (n + 16 * want - 1) / (16 * want);
-    p.ns = (n + p.stride - 1) / p.stride;
-    p.nb = (p.ns + 15) / 16;
-    while ((1 << p.log_nb) < p.nb) p.log_nb += 1;
-    const int share = (n + p.nb - 1) / p.nb;
-    p.cap = share <= kBucketSmall / 3 ? kBucketSmall : share <= kBucketMost / 4 ? 4 * share : kBucketMost;
-    // 8-byte words: entries (16 bytes each, aligned: first), splitters, fills,
-    // sorted rectangles, samples (4 bytes each)
-    p.words = 2 * (size_t)p.nb * p.cap + 2 * (size_t)p.nb + (size_t)n + ((size_t)p.ns + 1) / 2;
-    return p;
-}
-
 DepthScratch depth_scratch(const DepthPlan &dp, int n, void *base) {
     DepthScratch d{};
     d.entries = static_cast<uint4 *>(base);
@@ -614,6 +590,7 @@ void launch_depth_samplesort(const DepthPlan &dp, const DepthScratch &d, int n, 
         kernel<<<(dp.ns + per - 1) / per, kRankThreads, 0, st>>>(d.samples, dp.ns, dp.stride, n, dp.nb,
                                                                  d.splitters, d.fill);
     };
+    static_assert(64 * kRankBlocks >= kDepthSamples, "the largest instance ranks every sample");
     if (dp.ns <= 16 * kRankBlocks) split(depth_splitters_kernel<4>, 16);
     else if (dp.ns <= 32 * kRankBlocks) split(depth_splitters_kernel<8>, 32);
     else split(depth_splitters_kernel<16>, 64);

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include "depth_plan.h"
 #include "tgs.h"
 
 namespace tgs {
@@ -289,26 +290,17 @@ void launch_depth_sort(int n, uint32_t *count, const ushort4 *rect, const uint32
                        HostCounters *host, uint32_t tag, hipStream_t st);
 
 // ---- launchers (k_depthsort.hip) ----
-// Depth order of the Gaussians that have keys by a sample sort: sizes for a
-// scene of n Gaussians on a grid of n_tiles (ok: taken at all), the parts of its scratch (words
-// 8-byte words) and the sort, with the outputs of launch_depth_sort and the
-// sorted Gaussians' rectangles (DepthScratch::srect).  Without keys to
-// publish, because a bucket overflowed: HostCounters::redo.
-struct DepthPlan {
-    bool ok;
-    int stride, ns;     // samples: one per stride Gaussians
-    int nb, log_nb;     // buckets
-    uint32_t cap;       // entries of a bucket's region
-    size_t words;
-};
+// Depth order of the Gaussians that have keys by a sample sort (sizes:
+// depth_plan.h): the parts of its scratch and the sort, with the outputs of
+// launch_depth_sort and the sorted Gaussians' rectangles
+// (DepthScratch::srect).  Without keys to publish, because a bucket
+// overflowed: HostCounters::redo.
 struct DepthScratch {
     uint4 *entries;
     uint64_t *splitters, *fill;
     ushort4 *srect;
     uint32_t *samples;
 };
-constexpr int kDepthSamples = 16384;   // at most
-DepthPlan depth_plan(int n, int n_tiles);
 DepthScratch depth_scratch(const DepthPlan &dp, int n, void *base);
 void launch_depth_samplesort(const DepthPlan &dp, const DepthScratch &d, int n, const uint32_t *dkey,
                              const ushort4 *rect, const uint32_t *sat, int TX, uint32_t *didx,

@@ -78,3 +78,26 @@ def test_stress_full_size():
     st = temporal_parity(w.scene, w.cameras, W, H, "stress 3M 4K", sample_tiles=sample,
                          by_range=True, margin_px_frac=3e-3)
     assert st["kinds"][0] == O.TRUE_REF and st["tgs"] >= 1
+
+
+# the most Gaussians that the sample sort by depth takes (2048 buckets, their
+# regions full to a quarter), one more (radix passes of large partitions), and
+# one more than leaves room for half a tile id of 16 bits beside the index (a
+# tile sort of words)
+@pytest.mark.parametrize("n,W,H", [((1 << 23) - 1, 320, 200), (1 << 23, 320, 200), ((1 << 24) + 1, 4096, 4096)])
+@pytest.mark.timeout(600)
+def test_most_gaussians(n, W, H):
+    """Scenes at the largest sizes of the depth and tile sorts, nearly all
+    Gaussians visible, depths tied by the thousand: lists bit-exact, colour
+    and moments on sampled tiles, and no frame rendered twice."""
+    sc = synth.scene_uniform_cube(n, 7, degree=0, log_scale_mean=-7.0)
+    cam = synth.make_camera(synth.look_at((0.0, -4.0, 0.0), (0, 0, 0)), W, H)
+    TX, TY = cam.tiles
+    sample = np.random.default_rng(1).choice(TX * TY, 12, replace=False)
+    tgs.tgs_profile_start()
+    # lists of tens of thousands of entries, as in the stress scene: more
+    # pixels take a decision within the oracle's margin (1 of 896 measured)
+    full_parity(sc, [cam], sample_tiles=sample, label=f"{n} Gaussians {W}x{H}", margin_px_frac=3e-3)
+    # (the key buffers grow once where 4n + 65536 keys are not enough)
+    frames = tgs.tgs_profile_stop()["preprocess"]["launches"]
+    assert frames == 1, frames

@@ -99,10 +99,12 @@ __device__ inline uint32_t order_bucket_start(const OrderK &o, uint32_t c, int n
     const uint32_t ns = __shfl(inc, fit ? 63 - __clzll((long long)fit) : 0);
     if (o.n_split && tid == 0) *o.n_split = fit ? ns : 0u;
     const uint64_t nz = __ballot(c != 0u);
-    // the host reads this value some frames later: no fence needed
-    if (o.max_bucket && tid == 0)
-        __hip_atomic_store(o.max_bucket, nz ? (uint32_t)(32 - (__ffsll((long long)nz) - 1)) : 0u,
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    // the host reads this value some frames later: no fence needed (a frame
+    // without keys, for one that is about to be rendered again, says nothing
+    // of the next one's lists)
+    const int longest = nz ? 32 - (__ffsll((long long)nz) - 1) : 0;
+    if (o.max_bucket && tid == 0 && longest)
+        __hip_atomic_store(o.max_bucket, (uint32_t)longest, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     return inc - c;
 }
 

@@ -84,6 +84,7 @@ struct DevBuf {
 };
 
 constexpr uint32_t kUnknownKeys = 0xffffffffu;
+constexpr int kRadixFrames = 64;   // after an overflowed bucket: by other sorts (a second render per 64)
 
 // Per-frame scratch of one render path (a scene's tgs_render_full, or a state).
 struct Workspace {
@@ -99,7 +100,8 @@ struct Workspace {
     // frames that render every tile, [1] of selective-rendering frames
     uint32_t *host_maxb = nullptr;
     uint32_t *host_maxb_dev = nullptr;
-    bool radix_depth = false;             // depth order by radix passes, not by the sample sort
+    bool radix_depth = false;             // this frame: not by the sample sort
+    int radix_frames = 0;                 // frames still to come of which that is so
     bool frame_samples = false;           // this frame's depth order is by the sample sort
     bool general = false;                 // keys as (tile id, index) words whatever the plan says
     bool frame_seg = false;               // this frame orders tiles by the per-tile sort
@@ -112,6 +114,18 @@ struct Workspace {
                                                           // ([1]: selective rendering)
     const uint32_t *last_keys = nullptr, *last_vals = nullptr;
     bool has_frame = false;
+
+    // A bucket that overflowed says that the sampled Gaussians, the same ones
+    // every frame, do not tell the scene's depths from here: the frame is
+    // rendered again, and the next ones are spared a first try.
+    void frame_begins() {
+        radix_depth = radix_frames > 0;
+        if (radix_depth) radix_frames -= 1;
+    }
+    void bucket_overflowed() {
+        radix_depth = true;
+        radix_frames = kRadixFrames;
+    }
 
     ~Workspace() {
         if (host_cnt) (void)hipHostFree(host_cnt);
@@ -374,6 +388,8 @@ struct tgs_scene {
     bool split_auto = true;
     int split_bucket = tgs::kSplitBucket;
     int split_max = tgs::kMaxSplit;
+    // Workspace::radix_frames of the allocation-free renders, which keep no workspace
+    mutable std::atomic<int> noalloc_radix_frames{0};
     DevBuf data;
     SceneDev view{};
     Workspace ws;
@@ -439,6 +455,11 @@ tgs_status step_preprocess(const tgs_scene *sc, Workspace &ws, const CamK &cam, 
 // 33: 59.3 / 70.3 and 58.8 / 70.0; 9k, 60: 63.2 / 73.8 and 61.9 / 72.2; 60k,
 // 66: 71.9 / 85.9 and 71.0 / 84.5; 120k, 200: 123.5 / 136.6 and 103.1 / 116.0;
 // temporal interval of 1.5M 1928 and 1755 us.)
+// Against the twelve launches of radix passes that stand in for the sample
+// sort, the per-tile sort has the better of it up to kSegNoSamples (full
+// render, us: 30k Gaussians 68 and 103, 120k 124 and 153, with long lists 186
+// and 199).
+constexpr int kSegNoSamples = 131072;
 constexpr int kSegSparseScene = 24576;
 constexpr uint32_t kSegSparseKeys = 24;
 constexpr int kSegSmallScene = 8192;
@@ -450,15 +471,17 @@ constexpr int kSegSmallScene = 8192;
 tgs_status step_scan(const tgs_scene *sc, Workspace &ws, const uint32_t *sat, int TX,
                      hipStream_t st, const uint32_t **sorted_didx) {
     const int n = sc->n;
-    // per frame: the per-tile sort in small and sparse scenes, and, where the
-    // sample sort by depth does not reach (2^23 Gaussians), in selective-rendering
-    // frames, whose keys are few beside the Gaussians; in all where a recent
-    // frame's lists fit the per-tile sort's LDS bound
+    // per frame: the per-tile sort in small and sparse scenes, and, where there
+    // is no sample sort by depth (2^23 Gaussians, or a bucket overflowed), up to
+    // kSegNoSamples Gaussians and in selective-rendering frames, whose keys are
+    // few beside the Gaussians; in all where a recent frame's lists fit the
+    // per-tile sort's LDS bound
     const int nt = TX * ((ws.H + 15) / 16);
     const DepthPlan dp = depth_plan(n, nt);
     const uint32_t recent = ws.recent_K[sat ? 1 : 0];
     const bool sparse = n < kSegSparseScene && recent != kUnknownKeys && recent / kSegSparseKeys < (uint32_t)nt;
-    const bool prefer_seg = dp.ok ? n < kSegSmallScene || sparse : sat != nullptr;
+    const bool samples = dp.ok && ws.dsort.p && !ws.radix_depth;
+    const bool prefer_seg = samples ? n < kSegSmallScene || sparse : n < kSegNoSamples || sat != nullptr;
     const uint32_t maxb = ws.host_maxb ? reinterpret_cast<volatile uint32_t *>(ws.host_maxb)[sat ? 1 : 0]
                                        : 0xffffffffu;
     ws.frame_samples = false;
@@ -476,8 +499,8 @@ tgs_status step_scan(const tgs_scene *sc, Workspace &ws, const uint32_t *sat, in
         *sorted_didx = ws.didx.as<uint32_t>();
         return TGS_OK;
     }
-    ws.frame_samples = dp.ok && ws.dsort.p && !ws.radix_depth;
-    if (ws.frame_samples) {
+    ws.frame_samples = samples;
+    if (samples) {
         ProfScope ps(TGS_PROF_SORT, st);
         ws.seq += 1;
         launch_depth_samplesort(dp, depth_scratch(dp, n, ws.dsort.p), n, ws.dkey.as<uint32_t>(),
@@ -551,7 +574,7 @@ tgs_status step_wait_counters(Workspace &ws, hipStream_t st, FrameResult &fr, bo
 tgs_status grow_after_overflow(Workspace &ws, const FrameResult &fr, bool packed, hipStream_t st) {
     TGS_HIP(hipStreamSynchronize(st));
     if (fr.redo) {   // the buffers are large enough, the depth order was not found
-        ws.radix_depth = true;
+        ws.bucket_overflowed();
         return TGS_OK;
     }
     const size_t want = (size_t)fr.K + fr.K / 4 + 65536;
@@ -924,7 +947,7 @@ tgs_status tgs_render_full(tgs_scene *sc, const tgs_camera *cam, tgs_frame_out *
     const int W = cam->width, H = cam->height, TX = (W + 15) / 16, TY = (H + 15) / 16;
     Workspace &ws = sc->ws;
     TGS_TRY(ws.prepare(sc->n, W, H));
-    ws.radix_depth = false;
+    ws.frame_begins();
     const CamK ck = make_camk(cam);
     const bool packed = tile_sort_plan(sc->n, tile_id_bits(TX, TY)).packed;
     TGS_TRY(ws.ensure_keys(ws.key_cap ? ws.key_cap : 4 * (size_t)sc->n + 65536, packed));
@@ -1118,8 +1141,10 @@ tgs_status tgs_render_full_noalloc(const tgs_scene *sc, const tgs_camera *cam, t
     const CamK ck = make_camk(cam);
     FrameResult fr;
     bool overflow = false;
+    ws.radix_frames = sc->noalloc_radix_frames.load(std::memory_order_relaxed);
+    ws.frame_begins();
     do {
-        ws.radix_depth = fr.redo;   // (a second time round: with the radix passes)
+        if (fr.redo) ws.bucket_overflowed();
         // the counters read back must start clear: the array keeps the last
         // call's contents
         launch_fill_u8(reinterpret_cast<uint8_t *>(ws.host_cnt_dev), sizeof(HostCounters), 0, st);
@@ -1141,6 +1166,7 @@ tgs_status tgs_render_full_noalloc(const tgs_scene *sc, const tgs_camera *cam, t
         TGS_LAUNCHED("blend");
         TGS_TRY(step_wait_counters(ws, st, fr, &overflow));
     } while (fr.redo);
+    sc->noalloc_radix_frames.store(ws.radix_frames, std::memory_order_relaxed);
     if (overflow)
         return fail(TGS_ERR_CAPACITY, "frame needs " + std::to_string(fr.K) +
                                           " Gaussian-tile keys; the allocation-free render holds " +
@@ -1220,7 +1246,7 @@ tgs_status tgs_render_temporal(tgs_state *s, const tgs_camera *cam, tgs_frame_ou
     const int W = s->W, H = s->H, TX = s->TX, TY = s->TY, nt = TX * TY;
     Workspace &ws = s->ws;
     TGS_TRY(ws.prepare(sc->n, W, H));
-    ws.radix_depth = false;
+    ws.frame_begins();
     const CamK ck = make_camk(cam);
     const tgs_params &p = s->p;
 

@@ -197,7 +197,7 @@ void launch_ranges(uint32_t cap, const Counters *cnt, const uint32_t *keys, uint
 // *n_dev when n_dev is given, else n) in blend order, longest lists first,
 // into tile_out[0..m).
 // max_bucket (optional, host-visible memory) receives floor(log2 of the
-// longest list length) + 1 (0: all lists empty).
+// longest list length) + 1, and nothing where all lists are empty.
 struct OrderK {
     int n_host;
     const uint32_t *n_dev;

@@ -383,6 +383,43 @@ def test_depth_order_bucket_overflow():
             assert np.array_equal(v.cpu().numpy(), want[k]), k
 
 
+def _overflowing_scene(n=20_000):
+    sc = synth.small_scene(n, 29, degree=0)
+    sampled = np.zeros(n, bool)
+    sampled[_depth_samples(n)] = True
+    rng = np.random.default_rng(3)
+    sc.means[:, 1] = np.where(sampled, rng.uniform(-1.0, 1.0, n), rng.uniform(0.0, 1e-4, n))
+    return sc
+
+
+def test_depth_order_bucket_overflow_is_remembered(sort_path):
+    """A scene whose buckets overflow is rendered twice in its first frame and
+    once in each of the 64 after it, full or temporal, whatever the path."""
+    import torch
+    sc = _overflowing_scene()
+    cam = synth.orbit_path(1, 4.0, 0.0, 0.0, 200, 120)[0]
+    for path in (sort_path, tgs.SORT_AUTO):
+        twice = path != tgs.SORT_PER_TILE
+        with Up(sc, sort=path) as h:
+            s = tgs.tgs_state_create(h, 200, 120, tgs.params())
+            out = tgs.alloc_frame(200, 120, sc.n)
+            for render in (lambda: tgs.tgs_render_full(h, cam, **out),
+                           lambda: tgs.tgs_render_temporal(s, cam, **out)):
+                launches, images = [], []
+                for _ in range(1 + 64 + 1):
+                    tgs.tgs_profile_start()
+                    info = render()
+                    torch.cuda.synchronize()
+                    launches.append(tgs.tgs_profile_stop()["preprocess"]["launches"])
+                    images.append(out["rgb"].clone())
+                assert launches[0] == 1 + twice and launches[1:65] == [1] * 64, (path, launches)
+                if info["frame_kind"] == tgs.TGS_FRAME_FULL:
+                    # then the sample sort is tried again
+                    assert launches[65] == 1 + twice, (path, launches[65])
+                    assert all(torch.equal(i, images[0]) for i in images[1:])
+            tgs.tgs_state_free(s)
+
+
 def test_full_parity_object_subset():
     w = synth.workload("object", n_gaussians=40_000)
     _full_parity(w.scene, [w.cameras[0], w.cameras[37]], label="object 40k")

@@ -43,8 +43,8 @@ constexpr int kScatterThreads = 512;
 constexpr int kBucketShort = 8192;    // buckets sorted with half the LDS of the longest
 
 // Members of a sub-bucket up to which it is ranked by compares: a compare per
-// member for each entry; beyond, the whole bucket is sorted by exchanges.
-constexpr uint32_t kCrowd = 128;
+// member for each entry; beyond, it is cut again.
+constexpr uint32_t kCrowd = 48;
 
 // A bucket's fill and keys in one word: Gaussians in the low kFillBits, keys
 // above (scenes of under 2^23 Gaussians and 2^40 (Gaussian, tile) pairs).
@@ -249,10 +249,21 @@ struct BucketIo {
     int n_pre;
 };
 
+// A crowded sub-bucket: its entries stand at kv[at, at + n), pre of those in
+// crowded sub-buckets come before them, and their places in the bucket's order
+// begin at fin.  Bounds of their differences (d) and indices (i).
+struct Crowd {
+    uint32_t at, n, pre, fin;
+    uint32_t dlo, dhi, ilo, ihi;
+};
+
 // LDS of a block of NT threads sorting a bucket of up to CAP entries.
 template <int CAP, int NT>
 struct BucketLds {
     static constexpr int kSub = 4 * NT;   // sub-buckets
+    static constexpr int kGroups = CAP / (kCrowd + 1);
+    Crowd crowd[kGroups];
+    uint32_t shift[kGroups];              // fin - pre of the cut before
     uint64_t kv[CAP];                     // keys by sub-bucket, then the sorted entries' key counts
     uint32_t cur[kSub];                   // sub-bucket sizes, starts, ends
     uint32_t scan[2 * (NT / 64)];
@@ -288,49 +299,210 @@ __device__ inline void bucket_range(uint32_t *s, uint32_t &lo, uint32_t &hi) {
     __syncthreads();
 }
 
-// F steps (distances h, h / 2, ...) of the bitonic merge of runs of k / 2 words,
-// 2^F words a thread: 2h <= k <= P, h >= 2^(F - 1).
-template <int F, int NT>
-__device__ inline void bitonic_steps(uint64_t *kv, uint32_t P, uint32_t k, uint32_t h) {
-    const uint32_t s = h >> (F - 1);
-    for (uint32_t i = threadIdx.x; i < P >> F; i += NT) {
-        const uint32_t a = (i & ~(s - 1u)) << F | (i & (s - 1u));
-        uint64_t x[1 << F];
+// How a bucket was cut into sub-buckets: by depth (its least: lo), or where
+// all depths are one by index (its least), shifted by sh.
+struct Cut {
+    uint32_t lo;
+    int sh;
+    bool one_depth;
+};
+
+// Places of a bucket's E entries where sub-buckets are crowded, to tmp[0, E).
+// On entry kv holds (difference, index) by sub-bucket and s.cur each one's end
+// (c: how they were cut).  Entries of the others are ranked by compares; those of the crowded ones are cut again,
+// every group of them into its share of the kSub sub-buckets over its own
+// least to largest difference (or index, where the difference is one), until
+// none is crowded.
+//
+// A group has 49 entries or more and so a dozen sub-buckets, and its bounds
+// differ (indices do); its least entry falls into the first of them and its
+// largest into the upper half: every cut takes each group apart, and its range
+// by a factor of ten or so, so the loop ends (31 bits of difference, 23 of
+// index; a plane seen head-on: one cut).
+//
+// Entries and places are read from memory (the cache) in every step, not held:
+// registers for them would be taken from buckets that are not crowded.
+template <int CAP, int NT>
+__device__ __attribute__((always_inline)) inline void rank_crowded(BucketLds<CAP, NT> &s, const uint4 *ent,
+                                                                   uint32_t E, const Cut &c, uint32_t *tmp) {
+    constexpr int kWaves = NT / 64, kSub = BucketLds<CAP, NT>::kSub, kPer = kSub / NT;
+    // an entry without a place: the group it was in (bits 16 - 30) and its sub-bucket
+    constexpr uint32_t kActive = 1u << 31;
+    static_assert(kSub <= 1 << 16 && CAP < 1 << 16, "packed words");
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    auto entry = [&](uint32_t i) {
+        const uint2 x = *reinterpret_cast<const uint2 *>(ent + i);
+        return make_uint2((c.one_depth ? x.y : x.x) - c.lo, x.y);
+    };
+    uint32_t lim = E;       // of kv
+    uint32_t cnt[kPer];     // sizes of the thread's own sub-buckets
 #pragma unroll
-        for (int e = 0; e < 1 << F; ++e) x[e] = kv[a + (uint32_t)e * s];
-        const bool up = (a & k) == 0u;
+    for (int k = 0; k < kPer; ++k) {
+        const int i = tid * kPer + k;
+        cnt[k] = s.cur[i] - (i ? s.cur[i - 1] : 0u);
+    }
+    for (int round = 0;; ++round) {
+        uint32_t mine = 0, tot;   // entries in crowded sub-buckets, and those << 16
 #pragma unroll
-        for (int f = F - 1; f >= 0; --f) {
+        for (int k = 0; k < kPer; ++k) mine += cnt[k] > kCrowd ? cnt[k] | 1u << 16 : 0u;
+        uint32_t p = bucket_scan<kWaves, uint32_t>(mine, s.scan, &tot);
+        const uint32_t ng = tot >> 16, act = tot & 0xffffu;
 #pragma unroll
-            for (int e = 0; e < 1 << F; ++e) {
-                if (e >> f & 1) continue;
-                const uint64_t u = x[e], v = x[e | 1 << f];
-                const bool swap = up == (u > v);
-                x[e] = swap ? v : u;
-                x[e | 1 << f] = swap ? u : v;
+        for (int k = 0; k < kPer; ++k) {
+            if (cnt[k] > kCrowd) {
+                uint32_t &end = s.cur[tid * kPer + k];
+                s.crowd[p >> 16] = Crowd{end - cnt[k], cnt[k], p & 0xffffu, end - cnt[k], ~0u, 0u, ~0u, 0u};
+                end = kActive | p >> 16;
+                p += cnt[k] | 1u << 16;
+            }
+        }
+        __syncthreads();
+#pragma unroll 2
+        for (uint32_t i = (uint32_t)tid; i < E; i += NT) {
+            const uint2 x = entry(i);
+            const uint32_t was = round ? tmp[i] : kActive | x.x >> c.sh;
+            if (!(was & kActive)) continue;
+            const uint32_t cell = was & 0xffffu, end = s.cur[cell];
+            // from a place in kv to one in the bucket's order
+            const uint32_t shift = round ? s.shift[was >> 16 & 0x7fffu] : 0u;
+            if (end & kActive) {
+                const uint32_t g = end & 0xffffu;
+                if (round) s.crowd[g].fin = s.crowd[g].at + shift;   // the same from each of its entries
+                tmp[i] = kActive | g << 16;
+            } else {
+                uint32_t q = cell ? s.cur[cell - 1u] : 0u;
+                if (q & kActive) q = s.crowd[q & 0xffffu].at + s.crowd[q & 0xffffu].n;
+                const uint64_t key = (uint64_t)x.x << 32 | x.y;
+                uint32_t r = q;
+                for (; q < end; ++q) r += s.kv[q] < key ? 1u : 0u;
+                tmp[i] = r + shift;
+            }
+        }
+        if (tot == 0u) return;   // block-uniform
+        __syncthreads();
+        // each group's bounds: a wave takes its share of kv
+        const uint32_t share = (lim + kWaves - 1) / kWaves, k0 = (uint32_t)wave * share, k1 = k0 + share;
+        for (uint32_t g0 = 0; g0 < ng; g0 += 64) {
+            const uint32_t gl = min(g0 + (uint32_t)lane, ng - 1u);
+            if (g0 + (uint32_t)lane < ng && (gl & (kWaves - 1)) == (uint32_t)wave)
+                s.shift[gl] = s.crowd[gl].fin - s.crowd[gl].pre;
+            const bool meets = g0 + (uint32_t)lane < ng && s.crowd[gl].at < k1 && s.crowd[gl].at + s.crowd[gl].n > k0;
+            for (uint64_t left = __ballot(meets); left != 0ull; left &= left - 1ull) {
+                Crowd &x = s.crowd[g0 + (uint32_t)(__ffsll((long long)left) - 1)];
+                uint32_t dl = ~0u, dh = 0u, il = ~0u, ih = 0u;
+                const uint32_t e = min(x.at + x.n, k1);
+                for (uint32_t i = max(x.at, k0) + (uint32_t)lane; i < e; i += 64) {
+                    const uint64_t key = s.kv[i];
+                    dl = min(dl, (uint32_t)(key >> 32));
+                    dh = max(dh, (uint32_t)(key >> 32));
+                    il = min(il, (uint32_t)key);
+                    ih = max(ih, (uint32_t)key);
+                }
+#pragma unroll
+                for (int o = 32; o >= 1; o >>= 1) {
+                    dl = min(dl, __shfl_xor(dl, o));
+                    dh = max(dh, __shfl_xor(dh, o));
+                    il = min(il, __shfl_xor(il, o));
+                    ih = max(ih, __shfl_xor(ih, o));
+                }
+                if (lane == 0) {
+                    atomicMin(&x.dlo, dl);
+                    atomicMax(&x.dhi, dh);
+                    atomicMin(&x.ilo, il);
+                    atomicMax(&x.ihi, ih);
+                }
             }
         }
 #pragma unroll
-        for (int e = 0; e < 1 << F; ++e) kv[a + (uint32_t)e * s] = x[e];
+        for (int k = 0; k < kPer; ++k) s.cur[k * NT + tid] = 0u;
+        __syncthreads();
+        // sub-buckets by the entries before a group (and so its neighbour's
+        // end where its own begin); conversions and products of the same
+        // factor keep the order
+        const float per = (float)kSub / (float)act;
+#pragma unroll 2
+        for (uint32_t i = (uint32_t)tid; i < E; i += NT) {
+            const uint2 v = entry(i);
+            const uint32_t was = tmp[i];
+            if (!(was & kActive)) continue;
+            const Crowd x = s.crowd[was >> 16 & 0x7fffu];
+            const uint32_t b0 = (uint32_t)((float)x.pre * per), b1 = (uint32_t)((float)(x.pre + x.n) * per);
+            const bool one = x.dlo == x.dhi;
+            const uint32_t a = one ? v.y - x.ilo : v.x - x.dlo, range = one ? x.ihi - x.ilo : x.dhi - x.dlo;
+            const float f = (float)(b1 - b0) / ((float)range + 1.0f);
+            const uint32_t cell = b0 + min((uint32_t)((float)a * f), b1 - b0 - 1u);
+            tmp[i] = was | cell;
+            atomicAdd(&s.cur[cell], 1u);
+        }
+        __syncthreads();
+        uint32_t sum = 0, all;
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            cnt[k] = s.cur[tid * kPer + k];
+            sum += cnt[k];
+        }
+        uint32_t o = bucket_scan<kWaves, uint32_t>(sum, s.scan, &all);
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            s.cur[tid * kPer + k] = o;
+            o += cnt[k];
+        }
+        __syncthreads();
+#pragma unroll 2
+        for (uint32_t i = (uint32_t)tid; i < E; i += NT) {
+            const uint2 v = entry(i);
+            const uint32_t was = tmp[i];
+            if (was & kActive) s.kv[atomicAdd(&s.cur[was & 0xffffu], 1u)] = (uint64_t)v.x << 32 | v.y;
+        }
+        __syncthreads();
+        lim = act;
     }
-    __syncthreads();
 }
 
-// Sorts the E words of kv by a bitonic network over the next power of two (at
-// most CAP; the words past E are filled with all ones, above every entry),
-// three steps to a pass over LDS.  Every thread of the block takes part in
-// every barrier.
-template <int NT>
-__device__ void bitonic_sort(uint64_t *kv, uint32_t E) {
-    uint32_t P = 2;
-    while (P < E) P <<= 1;
-    for (uint32_t i = E + threadIdx.x; i < P; i += NT) kv[i] = ~0ull;
+// The rest of bucket_sort where sub-buckets are crowded.
+template <int CAP, int NT>
+__device__ __attribute__((always_inline)) inline void bucket_crowded(const BucketIo &io, BucketLds<CAP, NT> &s,
+                                                                     const uint4 *ent, uint32_t E,
+                                                                     uint32_t pos0, unsigned long long key0,
+                                                                     const Cut &c) {
+    const int tid = threadIdx.x;
+    uint32_t *tmp = io.didx + pos0;   // the bucket's part of the output, not yet written
+    rank_crowded<CAP, NT>(s, ent, E, c, tmp);
     __syncthreads();
-    for (uint32_t k = 2; k <= P; k <<= 1) {
-        uint32_t h = k >> 1;
-        for (; h >= 4; h >>= 3) bitonic_steps<3, NT>(kv, P, k, h);
-        if (h == 2) bitonic_steps<2, NT>(kv, P, k, h);
-        else if (h == 1) bitonic_steps<1, NT>(kv, P, k, h);
+#pragma unroll 2
+    for (uint32_t i = (uint32_t)tid; i < E; i += NT) {
+        const uint4 x = ent[i];
+        s.kv[tmp[i]] = (uint64_t)x.w << 32 | x.z;
+    }
+    __syncthreads();
+    uint64_t *srect = reinterpret_cast<uint64_t *>(io.srect);
+    for (uint32_t p = (uint32_t)tid; p < E; p += NT) srect[pos0 + p] = s.kv[p];
+    __syncthreads();
+    uint32_t *s_cnt = reinterpret_cast<uint32_t *>(s.kv), *s_idx = s_cnt + CAP;
+#pragma unroll 2
+    for (uint32_t i = (uint32_t)tid; i < E; i += NT) {
+        const uint4 x = ent[i];
+        const uint32_t p = tmp[i];
+        s_cnt[p] = entry_keys(io, x);
+        s_idx[p] = x.y;
+    }
+    __syncthreads();
+    // exclusive prefix of the counts in sorted order, consecutive ones per thread
+    const uint32_t per = (E + NT - 1) / NT, p0 = min((uint32_t)tid * per, E), p1 = min(p0 + per, E);
+    uint32_t sum = 0, tot;
+    for (uint32_t p = p0; p < p1; ++p) sum += s_cnt[p];
+    uint32_t o = bucket_scan<NT / 64, uint32_t>(sum, s.scan, &tot);
+    for (uint32_t p = p0; p < p1; ++p) {
+        const uint32_t n = s_cnt[p];
+        s_cnt[p] = o;
+        o += n;
+    }
+    __syncthreads();
+    for (uint32_t p = (uint32_t)tid; p < E; p += NT) {
+        const uint32_t a = s_cnt[p], e = p + 1u < E ? s_cnt[p + 1u] : tot;
+        io.didx[pos0 + p] = s_idx[p];
+        io.offs[pos0 + p] = sat32(key0 + a);
+        mark_key_blocks(io.kfirst, (uint32_t)key_blocks(io.key_cap), pos0 + p, key0 + a, e - a);
     }
 }
 
@@ -343,12 +515,13 @@ __device__ void bitonic_sort(uint64_t *kv, uint32_t E) {
 // sort took 45-100 us for 1.13M Gaussians, by the number of buckets.)  Where
 // all depths are one, the indices take their place.  Where more than kCrowd
 // entries share a range (planes seen head-on, two of them in one bucket), the
-// compares would grow with their number squared and the bucket is sorted by
-// exchanges instead: full render of 1.5M Gaussians on 64 planes 4615 -> 433 us
-// (on none 313 us; radix passes 362 us), 300k 465 -> 154 us (134; 234).
+// compares would grow with their number squared: it ends there, returns false
+// and leaves the rest to bucket_crowded, which is in the kernel once and not
+// for each IPT.
 template <int IPT, int CAP, int NT>
-__device__ void bucket_sort(const BucketIo &io, BucketLds<CAP, NT> &s, const uint4 *ent, uint32_t E,
-                            uint32_t pos0, unsigned long long key0) {
+__device__ __attribute__((always_inline)) inline bool bucket_sort(const BucketIo &io, BucketLds<CAP, NT> &s,
+                                                                  const uint4 *ent, uint32_t E, uint32_t pos0,
+                                                                  unsigned long long key0, Cut &cut) {
     constexpr int kWaves = NT / 64, kSub = BucketLds<CAP, NT>::kSub;
     const int tid = threadIdx.x;
     uint4 v[IPT];
@@ -403,24 +576,16 @@ __device__ void bucket_sort(const BucketIo &io, BucketLds<CAP, NT> &s, const uin
         if ((uint32_t)(j * NT + tid) < E)
             s.kv[atomicAdd(&s.cur[v[j].x >> sh], 1u)] = (uint64_t)v[j].x << 32 | v[j].y;
     const bool crowded = __syncthreads_or(most > kCrowd) != 0;
-    if (crowded) bitonic_sort<NT>(s.kv, E);   // block-uniform
+    if (crowded) {   // block-uniform
+        cut = Cut{lo, sh, one_depth};
+        return false;
+    }
     // (a counter now stands at its sub-bucket's end)
     uint32_t to[IPT];
 #pragma unroll
     for (int j = 0; j < IPT; ++j) {
         to[j] = 0u;
-        if (crowded) {   // its place: the entries below it
-            if ((uint32_t)(j * NT + tid) < E) {
-                const uint64_t mine = (uint64_t)v[j].x << 32 | v[j].y;
-                uint32_t a = 0u, e = E;
-                while (a < e) {
-                    const uint32_t mid = (a + e) / 2u;
-                    if (s.kv[mid] < mine) a = mid + 1u;
-                    else e = mid;
-                }
-                to[j] = a;
-            }
-        } else if ((uint32_t)(j * NT + tid) < E) {
+        if ((uint32_t)(j * NT + tid) < E) {
             const uint32_t b = v[j].x >> sh, end = s.cur[b];
             const uint64_t mine = (uint64_t)v[j].x << 32 | v[j].y;
             uint32_t q = b ? s.cur[b - 1u] : 0u;
@@ -478,19 +643,23 @@ __device__ void bucket_sort(const BucketIo &io, BucketLds<CAP, NT> &s, const uin
         const uint32_t p = (uint32_t)(j * NT + tid);
         if (p < E) srect[pos0 + p] = s.kv[p];
     }
+    return true;
 }
 
-// With the fewest items per thread (a power of two up to MAX) that hold E.
+// With the fewest items per thread (a power of two up to MAX, or 12: sixteen
+// take more registers than a wave has here) that hold E.
 template <int MAX, int CAP, int NT>
-__device__ inline void bucket_sort_for(const BucketIo &io, BucketLds<CAP, NT> &s, const uint4 *ent, uint32_t E,
-                                       uint32_t pos0, unsigned long long key0) {
+__device__ __attribute__((always_inline)) inline bool bucket_sort_for(const BucketIo &io, BucketLds<CAP, NT> &s,
+                                                                      const uint4 *ent, uint32_t E, uint32_t pos0,
+                                                                      unsigned long long key0, Cut &cut) {
     if constexpr (MAX > 1) {
-        if (E <= (uint32_t)(MAX / 2 * NT)) {   // block-uniform
-            bucket_sort_for<MAX / 2, CAP, NT>(io, s, ent, E, pos0, key0);
-            return;
-        }
+        if (E <= (uint32_t)(MAX / 2 * NT))   // block-uniform
+            return bucket_sort_for<MAX / 2, CAP, NT>(io, s, ent, E, pos0, key0, cut);
     }
-    bucket_sort<MAX, CAP, NT>(io, s, ent, E, pos0, key0);
+    if constexpr (MAX == 16) {
+        if (E <= (uint32_t)(12 * NT)) return bucket_sort<12, CAP, NT>(io, s, ent, E, pos0, key0, cut);
+    }
+    return bucket_sort<MAX, CAP, NT>(io, s, ent, E, pos0, key0, cut);
 }
 
 // Block b sorts bucket b if it holds more than MIN and at most CAP entries
@@ -555,8 +724,10 @@ __global__ __launch_bounds__(NT) void depth_buckets_kernel(BucketIo io) {
         }
     }
     if (over || E == 0u || E > (uint32_t)CAP) return;   // block-uniform
-    bucket_sort_for<CAP / NT, CAP, NT>(io, s, io.entries + (size_t)b * io.cap, E, fill_of(pre),
-                                               pre >> kFillBits);
+    const uint4 *ent = io.entries + (size_t)b * io.cap;
+    Cut cut;
+    if (!bucket_sort_for<CAP / NT, CAP, NT>(io, s, ent, E, fill_of(pre), pre >> kFillBits, cut))
+        bucket_crowded<CAP, NT>(io, s, ent, E, fill_of(pre), pre >> kFillBits, cut);
 }
 
 template <int IPT>

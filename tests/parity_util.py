@@ -2,10 +2,15 @@
 C-ABI, run the oracle on the same inputs, compare element by element."""
 from __future__ import annotations
 
+import os
+import subprocess
+
 import numpy as np
 
 from oracle import oracle as O
 from paper_2607_03390_amd import tgs
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2607_03390_amd", "csrc")
 
 # Per-channel colour tolerance (absolute, on [0,1] colours).
 RGB_TOL = 2e-4
@@ -25,6 +30,40 @@ STITCH_TOL = 1e-5
 
 def log(msg):
     print(msg, flush=True)
+
+
+def depth_plans(directory, pairs):
+    """The sample sort's sizes for (n, n_tiles) pairs, by the library's own
+    header: (ok, stride, samples, buckets, log2 of them, entries of a region)."""
+    src, exe = os.path.join(str(directory), "plan.cpp"), os.path.join(str(directory), "plan")
+    if not os.path.exists(exe):
+        with open(src, "w") as f:
+            f.write('#include <stdio.h>\n#include "depth_plan.h"\nint main(void) {\n'
+                    '    int n, t;\n    while (scanf("%d %d", &n, &t) == 2) {\n'
+                    '        const tgs::DepthPlan p = tgs::depth_plan(n, t);\n'
+                    '        printf("%d %d %d %d %d %u\\n", (int)p.ok, p.stride, p.ns, p.nb, p.log_nb, p.cap);\n'
+                    '    }\n    return 0;\n}\n')
+        subprocess.run(["g++", "-std=c++17", "-I", CSRC, "-o", exe, src], check=True)
+    text = "".join(f"{n} {t}\n" for n, t in pairs)
+    out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout
+    return [tuple(int(v) for v in line.split()) for line in out.splitlines()]
+
+
+def depth_samples(n, stride, ns):
+    """Indices of the Gaussians that the splitters are taken from."""
+    q = np.arange(ns, dtype=np.uint64)
+    at = q * stride + ((q * 0x9e3779b1 & 0xffffffff) * stride >> 32)
+    return np.minimum(at, n - 1).astype(np.int64)
+
+
+def depth_buckets(plan, place, n_visible):
+    """First place in the depth order of each bucket, and n_visible: place[i]
+    of Gaussian i (-1: it has no keys)."""
+    _, stride, ns, nb, _, _ = plan
+    got = place[depth_samples(place.size, stride, ns)]
+    ranked = np.sort(got[got >= 0])
+    cut = ranked[np.arange(1, nb) * ranked.size // nb] if ranked.size else np.full(nb - 1, n_visible)
+    return np.concatenate([[0], cut, [n_visible]])
 
 
 def gpu_full(scene_h, cam, n, depth=True, contrib=True):

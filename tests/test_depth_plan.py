@@ -7,35 +7,19 @@ in depth order.  For depths that know nothing of the order of the scene, all
 visible, their number is Poisson with mean cap / stride.
 """
 import math
-import os
-import subprocess
 
 import numpy as np
 import pytest
 
-CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2607_03390_amd", "csrc")
+from tests.parity_util import depth_buckets, depth_plans, depth_samples
+
 TOP = 1 << 23
 
 
 @pytest.fixture(scope="module")
 def plan(tmp_path_factory):
-    """(n, n_tiles) -> the plan's fields, by the library's own header."""
     d = tmp_path_factory.mktemp("plan")
-    src = d / "plan.cpp"
-    src.write_text('#include <stdio.h>\n#include "depth_plan.h"\nint main(void) {\n'
-                   '    int n, t;\n    while (scanf("%d %d", &n, &t) == 2) {\n'
-                   '        const tgs::DepthPlan p = tgs::depth_plan(n, t);\n'
-                   '        printf("%d %d %d %d %d %u\\n", (int)p.ok, p.stride, p.ns, p.nb, p.log_nb, p.cap);\n'
-                   '    }\n    return 0;\n}\n')
-    exe = d / "plan"
-    subprocess.run(["g++", "-std=c++17", "-I", CSRC, "-o", str(exe), str(src)], check=True)
-
-    def get(pairs):
-        text = "".join(f"{n} {t}\n" for n, t in pairs)
-        out = subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True).stdout
-        return [tuple(int(v) for v in line.split()) for line in out.splitlines()]
-
-    return get
+    return lambda pairs: depth_plans(d, pairs)
 
 
 def _sizes():
@@ -68,13 +52,9 @@ def test_sizes_that_take_other_sorts(plan):
 def test_random_depths_fill_no_region(plan, n):
     """The buckets of scenes of random depths, all visible: places of the
     sampled Gaussians in depth order, and the splitters among them."""
-    ((_, stride, ns, nb, _, cap),) = plan([(n, 1)])
-    q = np.arange(ns, dtype=np.uint64)
-    at = np.minimum(q * stride + ((q * 0x9e3779b1 & 0xffffffff) * stride >> 32), n - 1).astype(np.int64)
-    assert np.array_equal(at // stride, np.arange(ns))   # one per stratum
+    (p,) = plan([(n, 1)])
+    _, stride, ns, _, _, cap = p
+    assert np.array_equal(depth_samples(n, stride, ns) // stride, np.arange(ns))   # one per stratum
     for seed in range(4):
-        place = np.random.default_rng(seed).permutation(n)
-        ranked = np.sort(place[at])
-        cut = ranked[np.arange(1, nb) * ns // nb]
-        fill = np.diff(np.concatenate([[0], cut, [n]]))
+        fill = np.diff(depth_buckets(p, np.random.default_rng(seed).permutation(n), n))
         assert fill.max() <= cap, (n, seed, int(fill.max()))

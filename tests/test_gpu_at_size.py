@@ -18,7 +18,8 @@ import pytest
 
 from oracle import oracle as O
 from paper_2607_03390_amd import synth, tgs
-from tests.parity_util import full_parity, log, sample_tiles_for, temporal_parity
+from tests.parity_util import (depth_buckets, depth_plans, full_parity, log, sample_tiles_for,
+                               temporal_parity)
 
 pytestmark = pytest.mark.gpu
 
@@ -101,3 +102,38 @@ def test_most_gaussians(n, W, H):
     # (the key buffers grow once where 4n + 65536 keys are not enough)
     frames = tgs.tgs_profile_stop()["preprocess"]["launches"]
     assert frames == 1, frames
+
+
+# buckets of 256 and 512 regions, in one launch and in two; planes of several
+# buckets each and several planes to a bucket; planes an ulp apart
+@pytest.mark.parametrize("n,planes,apart", [(400_000, 3, 0.0), (1_500_000, 64, 0.0), (1_500_000, 500, 0.0),
+                                            (1_500_000, 40, 2.0 ** -22), (3_100_000, 200, 0.0)])
+@pytest.mark.timeout(300)
+def test_planes_seen_head_on(tmp_path, n, planes, apart):
+    """Depth order of scenes on planes seen head-on, whose buckets are crowded
+    at few depths: lists bit-exact.  By the plan's own buckets, the largest that
+    hold several depths, one of them with more entries than are ranked by
+    compares, take the largest instances."""
+    rng = np.random.default_rng(n + planes)
+    sc = synth.scene_uniform_cube(n, 7, degree=0, log_scale_mean=-6.0)
+    level = apart * np.arange(planes) if apart else rng.uniform(-1.0, 1.0, planes)
+    on = rng.random(n) >= 0.02
+    sc.means[:, 1] = np.where(on, level[rng.integers(0, planes, n)], sc.means[:, 1])
+    cam = synth.make_camera(synth.look_at((0.0, -4.0, 0.0), (0, 0, 0)), 320, 200)
+    g = O.gaussians(sc, cam)
+    vis = np.flatnonzero(g["status"] == O.VISIBLE)
+    order = vis[np.argsort(g["depth"][vis], kind="stable")]
+    place = np.full(n, -1, np.int64)
+    place[order] = np.arange(order.size)
+    (plan,) = depth_plans(tmp_path, [(n, 260)])
+    edge = depth_buckets(plan, place, order.size)
+    depth = g["depth"][order]
+    crowded = [0]
+    for a, b in zip(edge[:-1], edge[1:]):
+        many = np.unique(depth[a:b], return_counts=True)[1]
+        if many.size > 1 and many.max() > 48:
+            crowded.append(int(b - a))
+    log(f"[planes] {len(crowded) - 1} of {plan[3]} buckets crowded, the largest of {max(crowded)}")
+    assert max(crowded) > (8192 if n > 2_000_000 else 1024)
+    sample = np.random.default_rng(1).choice(260, 8, replace=False)
+    full_parity(sc, [cam], sample_tiles=sample, label=f"{n} on {planes} planes", margin_px_frac=3e-3)

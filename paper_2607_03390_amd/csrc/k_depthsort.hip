@@ -42,8 +42,13 @@ constexpr int kRankBlocks = 256;      // of the splitter kernel, at most: one pe
 constexpr int kScatterThreads = 512;
 constexpr int kBucketShort = 8192;    // buckets sorted with half the LDS of the longest
 
-// Members of a sub-bucket up to which it is ranked by compares: a compare per
-// member for each entry; beyond, it is cut again.
+// Members of a sub-bucket up to which a bucket is ranked by compares: a compare
+// per member for each entry.  Where one has more, those of more than kCrowd
+// are cut again.  The cuts have their own cost, and a bucket between a near and a
+// far part of a scene reaches a hundred at its ends: a room of 1.5M, whose
+// slowest bucket is one, 33.0 us on average by compares and 42.7 cut again from
+// 49 on.
+constexpr uint32_t kCrowdMost = 128;
 constexpr uint32_t kCrowd = 48;
 
 // A bucket's fill and keys in one word: Gaussians in the low kFillBits, keys
@@ -513,7 +518,7 @@ __device__ __attribute__((always_inline)) inline void bucket_crowded(const Bucke
 // of about one entry: placed by LDS counters, ranked inside by comparing
 // (difference, index) with each other member.  (Three passes of an LDS radix
 // sort took 45-100 us for 1.13M Gaussians, by the number of buckets.)  Where
-// all depths are one, the indices take their place.  Where more than kCrowd
+// all depths are one, the indices take their place.  Where more than kCrowdMost
 // entries share a range (planes seen head-on, two of them in one bucket), the
 // compares would grow with their number squared: it ends there, returns false
 // and leaves the rest to bucket_crowded, which is in the kernel once and not
@@ -575,7 +580,7 @@ __device__ __attribute__((always_inline)) inline bool bucket_sort(const BucketIo
     for (int j = 0; j < IPT; ++j)
         if ((uint32_t)(j * NT + tid) < E)
             s.kv[atomicAdd(&s.cur[v[j].x >> sh], 1u)] = (uint64_t)v[j].x << 32 | v[j].y;
-    const bool crowded = __syncthreads_or(most > kCrowd) != 0;
+    const bool crowded = __syncthreads_or(most > kCrowdMost) != 0;
     if (crowded) {   // block-uniform
         cut = Cut{lo, sh, one_depth};
         return false;

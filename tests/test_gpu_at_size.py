@@ -131,7 +131,7 @@ def test_planes_seen_head_on(tmp_path, n, planes, apart):
     crowded = [0]
     for a, b in zip(edge[:-1], edge[1:]):
         many = np.unique(depth[a:b], return_counts=True)[1]
-        if many.size > 1 and many.max() > 48:
+        if many.size > 1 and many.max() > 128:
             crowded.append(int(b - a))
     log(f"[planes] {len(crowded) - 1} of {plan[3]} buckets crowded, the largest of {max(crowded)}")
     assert max(crowded) > (8192 if n > 2_000_000 else 1024)

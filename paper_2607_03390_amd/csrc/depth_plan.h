@@ -16,7 +16,8 @@ struct DepthPlan {
     int stride, ns;     // samples: one per stride Gaussians
     int nb, log_nb;     // buckets
     uint32_t cap;       // entries of a bucket's region
-    size_t words;       // 8-byte words of scratch
+    size_t entries;     // bytes of all regions
+    size_t words;       // 8-byte words of the other scratch
 };
 
 // A bucket per CU while they hold up to 6144 Gaussians each (of whom half to
@@ -44,9 +45,9 @@ inline DepthPlan depth_plan(int n, int n_tiles) {
     while ((1 << p.log_nb) < p.nb) p.log_nb += 1;
     const int share = (n + p.nb - 1) / p.nb;
     p.cap = share <= kBucketSmall / 3 ? kBucketSmall : share <= kBucketMost / 4 ? 4 * share : kBucketMost;
-    // entries (16 bytes each, aligned: first), splitters, fills, sorted
-    // rectangles, samples (4 bytes each)
-    p.words = 2 * (size_t)p.nb * p.cap + 2 * (size_t)p.nb + (size_t)n + ((size_t)p.ns + 1) / 2;
+    p.entries = 16 * (size_t)p.nb * p.cap;
+    // splitters, fills, sorted rectangles, samples (4 bytes each)
+    p.words = 2 * (size_t)p.nb + (size_t)n + ((size_t)p.ns + 1) / 2;
     return p;
 }
 

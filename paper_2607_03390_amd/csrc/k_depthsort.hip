@@ -747,10 +747,10 @@ void scatter(const DepthPlan &dp, int n, const uint32_t *dkey, const ushort4 *re
 
 }  // namespace
 
-DepthScratch depth_scratch(const DepthPlan &dp, int n, void *base) {
+DepthScratch depth_scratch(const DepthPlan &dp, int n, void *entries, void *rest) {
     DepthScratch d{};
-    d.entries = static_cast<uint4 *>(base);
-    d.splitters = reinterpret_cast<uint64_t *>(d.entries + (size_t)dp.nb * dp.cap);
+    d.entries = static_cast<uint4 *>(entries);
+    d.splitters = static_cast<uint64_t *>(rest);
     d.fill = d.splitters + dp.nb;
     d.srect = reinterpret_cast<ushort4 *>(d.fill + dp.nb);
     d.samples = reinterpret_cast<uint32_t *>(d.srect + n);

@@ -91,7 +91,12 @@ struct Workspace {
     DevBuf g, rect, status, count, partial;
     DevBuf dkey, didx, offs;
     DevBuf dkey_alt, didx_alt;            // of the radix passes by depth, allocated with the first
-    DevBuf dsort;                         // scratch of the sample sort by depth
+    DevBuf dsort;                         // scratch of the sample sort by depth, without its entries
+    // the keys' values, twice (tval and tval_alt are views of it); the entries
+    // of the sample sort, which are done with when the keys are emitted, lie in
+    // the same memory (apart, a scene's first render, which allocates, took
+    // longer than by the radix passes)
+    DevBuf lists;
     DevBuf tkey, tval, tkey_alt, tval_alt, sort, segments, kfirst;
     DevBuf ranges, tile_len, sel, sel_list, sel_cols, sat, cnt, tile_order;
     HostCounters *host_cnt = nullptr;     // coherent pinned memory, written by the device
@@ -179,6 +184,21 @@ struct Workspace {
         return TGS_OK;
     }
 
+    // Bytes of `lists` for `keys` keys, and (samples) the entries of the sample
+    // sort of n Gaussians.
+    static size_t list_half(size_t keys) { return (keys * sizeof(uint32_t) + 255) & ~(size_t)255; }
+    static size_t list_bytes(size_t keys, int n, bool samples) {
+        const DepthPlan dp = depth_plan(n, 1);
+        const size_t b = list_half(keys) + keys * sizeof(uint32_t);
+        return samples && dp.ok && dp.entries > b ? dp.entries : b;
+    }
+    void split_lists(size_t keys) {
+        tval.borrow(lists.p, keys * sizeof(uint32_t));
+        tval_alt.borrow(lists.as<char>() + list_half(keys), keys * sizeof(uint32_t));
+    }
+
+    DepthScratch depth_parts(const DepthPlan &dp) const { return depth_scratch(dp, n, lists.p, dsort.p); }
+
     // Key buffers and sort scratch for at least `want` keys (capped at the
     // key limit).  Called before a frame is enqueued, or after an overflowed
     // frame has drained: the stream holds no work that uses them.
@@ -192,9 +212,9 @@ struct Workspace {
         last_K = 0;
         // (a buffer that is large enough stays as it is)
         TGS_TRY(tkey.ensure(packed ? want + 16 : want * sizeof(uint32_t)));
-        TGS_TRY(tval.ensure(want * sizeof(uint32_t)));
+        TGS_TRY(lists.ensure(list_bytes(want, n, true)));
+        split_lists(want);
         if (!packed) TGS_TRY(tkey_alt.ensure(want * sizeof(uint32_t)));
-        TGS_TRY(tval_alt.ensure(want * sizeof(uint32_t)));
         TGS_TRY(kfirst.ensure(key_blocks(want) * sizeof(uint32_t)));
         if (packed) TGS_TRY(segments.ensure(tile_sort_segment_words((uint32_t)want) * sizeof(uint32_t)));
         key_cap = want;
@@ -211,7 +231,7 @@ struct Workspace {
         return Records{g.as<float4>(),
                        rect.as<ushort4>(),   status.as<uint8_t>(),  count.as<uint32_t>(),
                        dkey.as<uint32_t>(),  partial.as<uint32_t>(),
-                       dp.ok && dsort.p ? depth_scratch(dp, n, dsort.p).samples : nullptr,
+                       dp.ok && dsort.p ? depth_parts(dp).samples : nullptr,
                        (uint32_t)dp.stride,
                        dp.ok ? ((1ull << 40) + dp.stride - 1) / (uint64_t)dp.stride : 0ull};
     }
@@ -503,7 +523,7 @@ tgs_status step_scan(const tgs_scene *sc, Workspace &ws, const uint32_t *sat, in
     if (samples) {
         ProfScope ps(TGS_PROF_SORT, st);
         ws.seq += 1;
-        launch_depth_samplesort(dp, depth_scratch(dp, n, ws.dsort.p), n, ws.dkey.as<uint32_t>(),
+        launch_depth_samplesort(dp, ws.depth_parts(dp), n, ws.dkey.as<uint32_t>(),
                                 ws.rect.as<ushort4>(), sat, TX, ws.didx.as<uint32_t>(),
                                 ws.offs.as<uint32_t>(), ws.kfirst.as<uint32_t>(), ws.cnt.as<Counters>(),
                                 (uint32_t)ws.key_cap, ws.partial.as<uint32_t>(), preprocess_blocks(n),
@@ -610,7 +630,7 @@ tgs_status step_keys(const tgs_scene *sc, Workspace &ws, int TX, int TY, const u
     {
         ProfScope ps(TGS_PROF_DUPLICATE, st);
         launch_duplicate(n, cap, cnt, didx, ws.offs.as<uint32_t>(), ws.kfirst.as<uint32_t>(),
-                         ws.frame_samples ? depth_scratch(depth_plan(n, 1), n, ws.dsort.p).srect : ws.rect.as<ushort4>(),
+                         ws.frame_samples ? ws.depth_parts(depth_plan(n, 1)).srect : ws.rect.as<ushort4>(),
                          ws.frame_samples, sat, sel_cols, TX, TX * TY, tp,
                          ws.tkey.as<uint32_t>(), ws.tval.as<uint32_t>(), ws.ranges.as<uint2>(),
                          ws.tile_len.as<uint32_t>(),
@@ -1051,7 +1071,9 @@ struct Carve {
 // [base, base + cap), with packed keys or with (tile id, index) words; false
 // if it does not fit.  The words' layout sets the capacity of a size; packed
 // keys take less of the array, except for the count rows of very few keys,
-// and (samples) the sample sort by depth takes what they leave.
+// and (samples) the sample sort by depth takes what they leave.  (A full
+// render uses neither the selected tiles nor their tables; their bytes stay in
+// the layout, whose capacity every size keeps.)
 bool layout_full(Workspace &ws, char *base, size_t cap, int n, int W, int H, size_t key_cap, bool packed,
                  bool samples = false) {
     Carve c{base, cap, 0};
@@ -1071,12 +1093,12 @@ bool layout_full(Workspace &ws, char *base, size_t cap, int n, int W, int H, siz
               c.take(ws.sel_cols, nt * sizeof(int)) &&
               c.take(ws.sat, (size_t)TY * (TX + 1) * sizeof(uint32_t)) &&
               c.take(ws.cnt, sizeof(Counters)) && c.take(ws.sort, sort_words * sizeof(uint32_t)) &&
-              c.take(ws.tkey, packed ? key_cap + 16 : key_cap * 4) && c.take(ws.tval, key_cap * 4) &&
+              c.take(ws.tkey, packed ? key_cap + 16 : key_cap * 4) &&
+              c.take(ws.lists, Workspace::list_bytes(key_cap, n, samples)) &&
               (packed ? c.take(ws.segments, tile_sort_segment_words((uint32_t)key_cap) * 4) &&
                             c.take(ws.tile_len, nt * 4)
                       : c.take(ws.tkey_alt, key_cap * 4)) &&
               (!samples || c.take(ws.dsort, depth_plan(n, 1).words * 8)) &&
-              c.take(ws.tval_alt, key_cap * 4) &&
               c.take(ws.kfirst, key_blocks(key_cap) * sizeof(uint32_t));
     void *hc = ok ? c.raw(sizeof(HostCounters)) : nullptr;
     void *mb = hc ? c.raw(2 * sizeof(uint32_t)) : nullptr;
@@ -1092,6 +1114,7 @@ bool layout_full(Workspace &ws, char *base, size_t cap, int n, int W, int H, siz
     ws.H = H;
     ws.key_cap = key_cap;
     ws.general = !packed;
+    ws.split_lists(key_cap);
     return true;
 }
 

@@ -291,7 +291,8 @@ void launch_depth_sort(int n, uint32_t *count, const ushort4 *rect, const uint32
 
 // ---- launchers (k_depthsort.hip) ----
 // Depth order of the Gaussians that have keys by a sample sort (sizes:
-// depth_plan.h): the parts of its scratch and the sort, with the outputs of
+// depth_plan.h): the parts of its scratch (entries: 16-byte aligned, used only
+// until the sorted order is written) and the sort, with the outputs of
 // launch_depth_sort and the sorted Gaussians' rectangles
 // (DepthScratch::srect).  Without keys to publish, because a bucket
 // overflowed: HostCounters::redo.
@@ -301,7 +302,7 @@ struct DepthScratch {
     ushort4 *srect;
     uint32_t *samples;
 };
-DepthScratch depth_scratch(const DepthPlan &dp, int n, void *base);
+DepthScratch depth_scratch(const DepthPlan &dp, int n, void *entries, void *rest);
 void launch_depth_samplesort(const DepthPlan &dp, const DepthScratch &d, int n, const uint32_t *dkey,
                              const ushort4 *rect, const uint32_t *sat, int TX, uint32_t *didx,
                              uint32_t *offs, uint32_t *kfirst, Counters *cnt, uint32_t cap,

@@ -137,3 +137,30 @@ def test_planes_seen_head_on(tmp_path, n, planes, apart):
     assert max(crowded) > (8192 if n > 2_000_000 else 1024)
     sample = np.random.default_rng(1).choice(260, 8, replace=False)
     full_parity(sc, [cam], sample_tiles=sample, label=f"{n} on {planes} planes", margin_px_frac=3e-3)
+
+
+# the fewest Gaussians of regions four times a bucket's share, and the most of 256 buckets
+@pytest.mark.parametrize("n", [1_050_000, 1_572_864])
+def test_device_memory_of_the_depth_order(n):
+    """The regions of the sample sort lie in the memory of the keys: a scene's
+    frame buffers take no more than with radix passes by depth (their second
+    copy of keys and indices) and keys as word pairs, twice."""
+    import torch
+    sc = synth.scene_uniform_cube(n, 7, degree=0, log_scale_mean=-6.0)
+    cam = synth.make_camera(synth.look_at((0.0, -4.0, 0.0), (0, 0, 0)), 320, 200)
+    out = tgs.alloc_frame(320, 200)
+    h = tgs.tgs_scene_upload(sc)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    info = tgs.tgs_render_full(h, cam, **out)
+    torch.cuda.synchronize()
+    used = free - torch.cuda.mem_get_info()[0]
+    tgs.tgs_scene_free(h)
+    assert info["n_keys"] <= 4 * n + 65536   # no growth
+    # records, rectangles, status, count, depth key, index, offset; the copies;
+    # a sort's two count tables of 256 words per 1024 keys; the keys; and half a
+    # page of 2 MiB for each of two dozen buffers (188 and 240 MiB measured; with
+    # regions of their own 32 and 48 MiB more)
+    bound = n * (64 + 8 + 1 + 4 * 4 + 8) + (2 + 16) * (4 * n + 65536) + (24 << 20)
+    log(f"[memory] {n} Gaussians: {used >> 20} MiB, bound {bound >> 20} MiB")
+    assert used <= bound

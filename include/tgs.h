@@ -350,11 +350,12 @@ tgs_status tgs_scene_set_sort_path(tgs_scene *scene, int32_t mode);
  * block re-reads the whole list, so shorter ones are cheaper unsplit.
  * log2_min in [0, 31], or -1 for no split; max_tiles in [0,
  * TGS_BLEND_SPLIT_MAX].  A scene on which it was never called splits at most
- * TGS_BLEND_SPLIT_MAX tiles, from a threshold that follows each frame: its
+ * TGS_BLEND_SPLIT_MAX tiles, from a threshold that follows each frame.  It is
  * keys / 1024 rounded up to a power of two, at least 32 (64 from 513 tiles to
  * render on, 128 from 1025, 256 from 4097) and at most
- * 2^TGS_BLEND_SPLIT_DEFAULT (frames with few keys leave the chip idle behind
- * their longest lists).  INVALID_ARG for a NULL scene or other values. */
+ * 2^TGS_BLEND_SPLIT_DEFAULT; where the Gaussians have five keys or more each
+ * and it is below that bound, at most 256 if no more than 768 tiles hold 16
+ * entries, else the bound.  INVALID_ARG for a NULL scene or other values. */
 enum { TGS_BLEND_SPLIT_DEFAULT = 12, TGS_BLEND_SPLIT_MAX = 1024 };
 tgs_status tgs_scene_set_blend_split(tgs_scene *scene, int32_t log2_min, int32_t max_tiles);
 

@@ -17,32 +17,47 @@ namespace tgs {
 // Bucket of a list length: floor(log2(len)) + 1, 0 for an empty list.
 __device__ inline uint32_t length_bucket(uint32_t len) { return len ? 32u - (uint32_t)__clz(len) : 0u; }
 
-// Length bucket from which a frame of n_keys keys on n_tiles tiles to render
-// splits its tiles, at most most: lists of at least the keys that 1024 evenly
-// loaded blocks would each hold, rounded up to a power of two.  A list longer
-// than that is still walked when the rest of the chip has run dry (about
-// 2048 tile blocks are resident at once), so its tile sets the launch's tail
-// and four quadrant blocks shorten it; shorter ones are only staged four
-// times for nothing.  Frames with few keys have a lower bound besides: 32
-// where all tiles' quadrants are resident at once (512 tiles), and more on
-// larger grids, where quadrants of short lists are only more blocks to
-// launch.  Measured at thresholds of 2^5 .. 2^13 (blend launch, microseconds),
-// by the keys: 107k keys on 920 tiles with every output 54 up to 2^9, 88 at
-// 2^10, 149 at 2^12; 745k keys on 3600 tiles 59 up to 2^8, 69 at 2^10, 88 at
-// 2^12; 572k - 1.1M keys on the selected tiles of a room 72 up to 2^9, 58
-// from 2^10; 5.0M keys on 8160 tiles 101 - 110 at all.  By the grid: 34k
-// keys on 256 tiles 12 up to 2^7, 16 at 2^8, 22 from 2^9; 12k on 468 tiles 8.8
-// at 2^6, 9.8 at 2^7; 38k on 920 tiles 11.8 at 2^6, 14.6 at 2^7; 53k on 1600
-// tiles 15.0 at 2^6, 13.1 from 2^7; 72k on 3600 tiles 17.6 at 2^6, 16.1 at
-// 2^7, 18.3 at 2^8; 96k on 6300 tiles 17.3 at 2^7, 16.3 at 2^8.  (Of wide
-// opaque Gaussians few entries of a list are walked before the pixels stop,
-// and splitting at all costs up to a tenth: 532k keys on 3600 tiles 27.5 at
-// 2^12, 29.7 at 2^10, 35 at 2^8.  The lengths do not tell.)
-__device__ inline int split_bucket_for(uint32_t n_keys, int n_tiles, int most) {
+// Length bucket from which a frame splits its tiles, at most `most`: of n_keys
+// keys of n_visible Gaussians on n_tiles tiles to render, `busy` of them with
+// lists of 2^(kBusyBucket - 1) entries and more.  Splitting pays where a few
+// tiles are still walked when the rest of the chip has run dry (about 2048 tile
+// blocks are resident at once); everywhere else the quadrants only stage their
+// lists four times.
+//  - Narrow Gaussians (fewer than kWideKeys tiles each): a tile takes about as
+//    long as its list.  Split are lists of at least the keys that 1024 evenly
+//    loaded blocks would each hold, rounded up to a power of two.
+//  - Wide ones: pixels stop long before their lists end, so that the lengths
+//    say little; what counts is whether the tiles fill the chip.  With up to
+//    kFewTiles busy tiles, lists are split from 2^kFewLog entries on at the
+//    latest, with more as few as may be.
+// Either way a lower bound: 32 where all tiles' quadrants are resident at once
+// (512 tiles), and more on larger grids, where quadrants of short lists are
+// only more blocks to launch.
+//
+// Measured at thresholds of 2^5 .. 2^12 (blend launch, microseconds; 2^12 splits
+// hardly any tile).  Narrow: 107k keys on 920 tiles with every output 54 up to
+// 2^9, 88 at 2^10, 149 at 2^12; 745k on 3600 tiles 59 up to 2^8, 69 at 2^10, 88
+// at 2^12; 632k on 230 of 390 tiles 31 up to 2^8, 57 at 2^10, 85 from 2^11;
+// 201k on 8160 tiles 24 at 2^8, 32 from 2^10; 572k - 1.1M on the selected tiles
+// of a room 72 up to 2^9, 58 from 2^10; at worst 457k on 3600 tiles 42 at 2^9,
+// 38 from 2^10.  Wide, few tiles: 1.07M keys on 600 of 1000 tiles 35 at 2^7, 38
+// at 2^8, 55 at 2^10, 59 at 2^12.  Many: 531k on 1300 of 2280 tiles 42 to 49 up
+// to 2^10, 38 from 2^11; 1.77M on as many 54 to 64 up to 2^11, 44 at 2^12; 1.89M
+// on 3000 of 8160 72 up to 2^10, 62 at 2^11, 46 at 2^12; at worst 20k needles
+// on all of 1000 tiles 33 at 2^10, 39 at 2^12.  (By the first rule for all
+// frames those five took 62, 45, 58, 62 and 33.)  By the grid: 34k keys on 256
+// tiles 12 up to 2^7, 16 at 2^8, 22 from 2^9; 53k on 1600 tiles 15.0 at 2^6,
+// 13.1 from 2^7; 72k on 3600 tiles 17.6 at 2^6, 16.1 at 2^7, 18.3 at 2^8; 96k
+// on 6300 tiles 17.3 at 2^7, 16.3 at 2^8.
+constexpr uint32_t kWideKeys = 5, kFewTiles = 768;
+constexpr int kBusyBucket = 5, kFewLog = 8;
+__device__ inline int split_bucket_for(uint32_t n_keys, uint32_t n_visible, int n_tiles, uint32_t busy,
+                                       int most) {
     const uint32_t mean = n_keys >> 10;
     const int least = 5 + (n_tiles > 512) + (n_tiles > 1024) + (n_tiles > 4096);
     const int lg = mean > 1u << least ? 32 - __clz(mean - 1u) : least;
-    return lg + 1 < most ? lg + 1 : most;
+    if (lg + 1 >= most) return most;
+    return n_keys / kWideKeys < n_visible ? lg + 1 : busy > kFewTiles ? most : lg < kFewLog ? lg + 1 : kFewLog + 1;
 }
 
 constexpr int kOrderBuckets = 33;
@@ -93,8 +108,10 @@ __device__ inline uint32_t order_bucket_start(const OrderK &o, uint32_t c, int n
     // the tiles the blend splits, a prefix of the order: those of the
     // buckets from the lowest one >= split_bucket that leaves at most
     // max_split tiles in it and above (whole buckets)
-    const int sb = o.n_keys && o.split_bucket >= 1 ? split_bucket_for(*o.n_keys, n, o.split_bucket)
-                                                   : o.split_bucket;
+    const uint32_t busy = __shfl(inc, 32 - kBusyBucket);
+    const int sb = o.cnt && o.split_bucket >= 1
+                       ? split_bucket_for(o.cnt->n_sorted, o.cnt->n_visible, n, busy, o.split_bucket)
+                       : o.split_bucket;
     const uint64_t fit = __ballot(sb >= 1 && b >= sb && inc <= (uint32_t)o.max_split);
     const uint32_t ns = __shfl(inc, fit ? 63 - __clzll((long long)fit) : 0);
     if (o.n_split && tid == 0) *o.n_split = fit ? ns : 0u;

@@ -648,7 +648,7 @@ tgs_status step_keys(const tgs_scene *sc, Workspace &ws, int TX, int TY, const u
     order.n_split = &cnt->n_split;
     order.split_bucket = sc->split_bucket;
     order.max_split = sc->split_max;
-    order.n_keys = sc->split_auto ? &cnt->n_sorted : nullptr;
+    order.cnt = sc->split_auto ? cnt : nullptr;
     int alt = 0;
     if (tp.packed) {
         ProfScope ps(TGS_PROF_SORT, st);

@@ -209,12 +209,12 @@ struct OrderK {
     // order: those whose list length bucket is at least split_bucket, or, if
     // more than max_split (<= kMaxSplit) are, at least the lowest higher
     // bucket that leaves at most max_split (0: no split)
-    // n_keys (optional): the frame's key count; split_bucket is then an upper
-    // bound and the frame's own is taken from its mean load (split_bucket_for)
+    // cnt (optional): the frame's counters; split_bucket is then an upper bound
+    // and the frame's own is taken from its keys and lists (split_bucket_for)
     uint32_t *n_split;
     int split_bucket;
     int max_split;
-    const uint32_t *n_keys;
+    const Counters *cnt;
 };
 // (kOrderShares blocks, each placing its share of the tiles.)
 constexpr int kOrderShares = 8;

@@ -209,9 +209,8 @@ def split_auto():
     SETTINGS["split"] = (tgs.BLEND_SPLIT_DEFAULT, tgs.BLEND_SPLIT_MAX)
 
 
-# fewer than 32 keys per 1024 (threshold 32), a threshold between the two
-# bounds, and one past the most tiles that are split; then the lower bounds of
-# larger grids (1600 and 4600 tiles)
+# the threshold's branches (test_split_auto_branches): 32, and two between the
+# bounds, by the keys of narrow Gaussians; wide ones on few and on many tiles
 @pytest.mark.parametrize("n,log_scale,W,H", [(700, -3.0, 200, 136), (24_000, -2.6, 48, 40),
                                              (20_000, -4.0, 641, 359), (6_000, -3.0, 800, 500),
                                              (6_000, -3.0, 1472, 800)])
@@ -221,6 +220,42 @@ def test_split_auto_full_parity(split_auto, n, log_scale, W, H):
     sc = synth.scene_uniform_cube(n, 11, degree=1, log_scale_mean=log_scale)
     cam = synth.make_camera(synth.look_at((0.3, -4.0, 0.5), (0, 0, 0)), W, H)
     _full_parity(sc, [cam], label=f"split auto {W}x{H}")
+
+
+def _split_of(sc, cam):
+    """The threshold (log2) that a frame of these Gaussians takes, and why."""
+    g = O.gaussians(sc, cam)
+    TX, TY = cam.tiles
+    counts = O.tile_counts(g, TX, TY)
+    ln, keys = np.diff(counts), int(counts[-1])
+    nt, mean = TX * TY, keys >> 10
+    least = 5 + (nt > 512) + (nt > 1024) + (nt > 4096)
+    lg = max(least, (max(mean, 1) - 1).bit_length())
+    if lg >= 12:
+        return 12, "keys"
+    if keys // 5 >= int((g["status"] == O.VISIBLE).sum()):
+        return (min(lg, 8), "few") if (ln >= 16).sum() <= 768 else (12, "many")
+    return lg, "long"
+
+
+def test_split_auto_branches():
+    """Where the scenes above stand in the choice of the threshold: the image of
+    the scene's own is the image of that fixed threshold, and not of another
+    that splits other tiles (the sums of a quadrant's pixels are taken in
+    another order)."""
+    eye = (0.3, -4.0, 0.5)
+    for n, log_scale, W, H, want in [(700, -3.0, 200, 136, (5, "long")), (24_000, -2.6, 48, 40, (6, "long")),
+                                     (20_000, -4.0, 641, 359, (7, "long")), (6_000, -3.0, 800, 500, (7, "few")),
+                                     (12_000, -2.3, 480, 300, (8, "few")), (6_000, -3.0, 1472, 800, (12, "many"))]:
+        sc = synth.scene_uniform_cube(n, 11, degree=1, log_scale_mean=log_scale)
+        cam = synth.make_camera(synth.look_at(eye, (0, 0, 0)), W, H)
+        assert _split_of(sc, cam) == want, (n, W, H, _split_of(sc, cam))
+        with Up(sc, split=None) as h:
+            own = gpu_full(h, cam, n)["rgb"]
+            tgs.tgs_scene_set_blend_split(h, want[0])
+            assert np.array_equal(gpu_full(h, cam, n)["rgb"], own), (n, W, H)
+            tgs.tgs_scene_set_blend_split(h, -1 if want[0] < 12 else 8)
+            assert not np.array_equal(gpu_full(h, cam, n)["rgb"], own), (n, W, H)
 
 
 def test_split_auto_temporal_parity(split_auto):

@@ -321,17 +321,21 @@ tgs_status tgs_profile_stop(tgs_profile *out);
  * tile) is produced, for every later render through `scene` (tgs_render_full
  * and the temporal states bound to it).  Both ways give identical per-tile
  * lists (depth bits, then Gaussian index):
- *   TGS_SORT_DEPTH_FIRST: the Gaussians with keys are sorted by depth (a
- *     sample sort; radix passes above 2^23 Gaussians), keys are emitted in
- *     that order and stably radix-sorted by tile;
+ *   TGS_SORT_DEPTH_FIRST: the Gaussians with keys are sorted by depth, keys
+ *     are emitted in that order and stably radix-sorted by tile.  The depth
+ *     sort is a sample sort; radix passes take its place from 2^23 Gaussians
+ *     or 2^40 (Gaussian, tile) pairs on, in a frame whose depths overflow one
+ *     of its buckets and in the 64 frames after it, and in allocation-free
+ *     renders whose scratch array has no room for it;
  *   TGS_SORT_PER_TILE: key counts are scanned in index order, keys emitted
  *     in index order and stably sorted by tile, then one block per tile
  *     sorts its list by (depth bits, index) in LDS (lists above 4096 entries
  *     take a slower in-block path);
  *   TGS_SORT_AUTO (default): per frame, the per-tile sort for scenes with
- *     fewer than 8192 Gaussians, for scenes with fewer than 24576 when a
- *     recent frame of the same kind had fewer than 24 keys per tile, and for
- *     TemporalGS frames where the sample sort does not reach, when the longest
+ *     fewer than 24576 Gaussians when a recent frame of the same kind had
+ *     fewer than 24 keys per tile (96 with fewer than 8192 Gaussians on up to
+ *     512 tiles), and, where radix passes take the sample sort's place, for
+ *     scenes with fewer than 131072 and for TemporalGS frames, when the longest
  *     tile list of a recent frame of the same kind has fewer than 4096
  *     entries; else the depth-first sort.
  * INVALID_ARG for a NULL scene or another value.  Like every call on a

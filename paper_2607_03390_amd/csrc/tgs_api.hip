@@ -463,18 +463,24 @@ tgs_status step_preprocess(const tgs_scene *sc, Workspace &ws, const CamK &cam, 
     return TGS_OK;
 }
 
-// Scenes below kSegSmallScene Gaussians sort each tile's list instead of the
-// Gaussians by depth where the lists are short: one launch fewer.  Up to
-// kSegSparseScene they do where the keys of a recent frame of the same kind
-// were at most kSegSparseKeys a tile: then a block per tile has next to
-// nothing to sort, while the sample sort still ranks and scatters every
-// Gaussian.  (Full render / frame of a temporal sequence, us, per-tile and by
-// depth, by Gaussians and keys a tile: 5k, 5: 54.4 / 65.4 and 57.1 / 68.8; 9k,
-// 10: 53.5 / 65.5 and 56.9 / 69.1; 16k, 9: 56.8 / 68.7 and 60.2 / 71.1; 16k,
-// 18: 57.7 / 68.4 and 59.1 / 71.7; 30k, 17: 60.3 / 72.3 and 60.4 / 72.4; 16k,
-// 33: 59.3 / 70.3 and 58.8 / 70.0; 9k, 60: 63.2 / 73.8 and 61.9 / 72.2; 60k,
-// 66: 71.9 / 85.9 and 71.0 / 84.5; 120k, 200: 123.5 / 136.6 and 103.1 / 116.0;
-// temporal interval of 1.5M 1928 and 1755 us.)
+// Scenes of fewer than kSegSparseScene Gaussians sort each tile's list instead
+// of the Gaussians by depth where the keys of a recent frame of the same kind
+// were at most kSegSparseKeys a tile: then a block per tile has next to nothing
+// to sort, while the sample sort still ranks and scatters every Gaussian.
+// Fewer than kSegSmallScene of them on up to kSegSmallGrid tiles (a block per
+// tile leaves CUs idle, and longer lists cost little) do up to kSegSmallKeys.
+// (Full render / frame of a temporal sequence, us, per-tile and by depth, by
+// Gaussians and keys a tile: 5k, 5: 54.4 / 65.4 and 57.1 / 68.8; 9k, 10: 53.5 /
+// 65.5 and 56.9 / 69.1; 16k, 9: 56.8 / 68.7 and 60.2 / 71.1; 16k, 18: 57.7 /
+// 68.4 and 59.1 / 71.7; 2k, 16: 81.0 / 95.8 and 79.4 / 96.0; 30k, 17: 60.3 /
+// 72.3 and 60.4 / 72.4; 500, 28: 74.0 / 81.4 and 69.9 / 79.8; 4k, 35: 83.4 /
+// 84.4 and 80.1 / 84.9; 16k, 33: 59.3 / 70.3 and 58.8 / 70.0; 9k, 60: 63.2 /
+// 73.8 and 61.9 / 72.2; 4k, 206: 113.6 / 102.8 and 98.4 / 96.4; 8k, 414: 170.2 /
+// 131.7 and 122.3 / 109.5; 120k, 200: 123.5 / 136.6 and 103.1 / 116.0; on 256
+// tiles: 2k, 55: 47.1 / 53.2 and 46.5 / 55.4; 8k, 82: 46.8 / 55.7 and 48.7 /
+// 56.2; 4k, 108: 53.0 / 57.2 and 51.8 / 58.4; 14k, 93: 49.6 / 56.5 and 48.9 /
+// 55.8; 8k, 217: 57.3 / 60.5 and 52.4 / 59.0; temporal interval of 1.5M 1928 and
+// 1755 us.)
 // Against the twelve launches of radix passes that stand in for the sample
 // sort, the per-tile sort has the better of it up to kSegNoSamples (full
 // render, us: 30k Gaussians 68 and 103, 120k 124 and 153, with long lists 186
@@ -483,6 +489,8 @@ constexpr int kSegNoSamples = 131072;
 constexpr int kSegSparseScene = 24576;
 constexpr uint32_t kSegSparseKeys = 24;
 constexpr int kSegSmallScene = 8192;
+constexpr int kSegSmallGrid = 512;
+constexpr uint32_t kSegSmallKeys = 96;
 
 // The Gaussians that have keys and the start of their keys, in the order the
 // keys are emitted: depth order (global depth sort; the last pass publishes
@@ -491,7 +499,7 @@ constexpr int kSegSmallScene = 8192;
 tgs_status step_scan(const tgs_scene *sc, Workspace &ws, const uint32_t *sat, int TX,
                      hipStream_t st, const uint32_t **sorted_didx) {
     const int n = sc->n;
-    // per frame: the per-tile sort in small and sparse scenes, and, where there
+    // per frame: the per-tile sort in small scenes of few keys, and, where there
     // is no sample sort by depth (2^23 Gaussians, or a bucket overflowed), up to
     // kSegNoSamples Gaussians and in selective-rendering frames, whose keys are
     // few beside the Gaussians; in all where a recent frame's lists fit the
@@ -499,9 +507,10 @@ tgs_status step_scan(const tgs_scene *sc, Workspace &ws, const uint32_t *sat, in
     const int nt = TX * ((ws.H + 15) / 16);
     const DepthPlan dp = depth_plan(n, nt);
     const uint32_t recent = ws.recent_K[sat ? 1 : 0];
-    const bool sparse = n < kSegSparseScene && recent != kUnknownKeys && recent / kSegSparseKeys < (uint32_t)nt;
+    const uint32_t most_keys = n < kSegSmallScene && nt <= kSegSmallGrid ? kSegSmallKeys : kSegSparseKeys;
+    const bool sparse = n < kSegSparseScene && recent != kUnknownKeys && recent / most_keys < (uint32_t)nt;
     const bool samples = dp.ok && ws.dsort.p && !ws.radix_depth;
-    const bool prefer_seg = samples ? n < kSegSmallScene || sparse : n < kSegNoSamples || sat != nullptr;
+    const bool prefer_seg = samples ? sparse : n < kSegNoSamples || sat != nullptr;
     const uint32_t maxb = ws.host_maxb ? reinterpret_cast<volatile uint32_t *>(ws.host_maxb)[sat ? 1 : 0]
                                        : 0xffffffffu;
     ws.frame_samples = false;

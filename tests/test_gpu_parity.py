@@ -96,22 +96,24 @@ def test_full_render_independent_of_earlier_sizes():
             assert np.array_equal(got[k], ref[k]), (k, c.width, c.height)
 
 
-def test_auto_sort_path_follows_the_frames(sort_path):
-    """The per-frame choice of the sort path (12k Gaussians: by depth, or per
-    tile after a sparse frame) at cameras that turn it over: every frame's
-    bits, and its keys and lists, are those of the scene that always sorts one
-    way."""
-    sc = synth.small_scene(12_000, 5, degree=1, log_scale_mean=-5.0)
+@pytest.mark.parametrize("n,log_scale,W,H,most", [(12_000, -5.0, 640, 400, 24), (4_000, -4.0, 640, 400, 24),
+                                                  (4_000, -3.5, 200, 136, 96)])
+def test_auto_sort_path_follows_the_frames(sort_path, n, log_scale, W, H, most):
+    """The per-frame choice of the sort path (by depth, or per tile after a
+    frame of few keys a tile) at cameras that turn it over: every frame's bits,
+    and its keys and lists, are those of the scene that always sorts one way."""
+    sc = synth.small_scene(n, 5, degree=1, log_scale_mean=log_scale)
     # few keys a tile, many, few; the frame after each takes the other path
-    cams = [synth.make_camera(synth.look_at((0.1, -d, 0.2), (0, 0, 0)), 640, 400)
+    cams = [synth.make_camera(synth.look_at((0.1, -d, 0.2), (0, 0, 0)), W, H)
             for d in (6.0, 6.0, 2.0, 2.0, 6.0, 6.0, 2.0)]
     runs = []
     for path in (tgs.SORT_AUTO, sort_path):
         with Up(sc, sort=path) as h:
             runs.append([(gpu_full(h, c, sc.n), tgs.tgs_debug_dump(h, None, tgs.TGS_DUMP_SORTED_VALUES))
                          for c in cams])
-    per_tile = [r["n_keys"] / 1000 for r, _ in runs[0]]
-    assert per_tile[0] < 24 < per_tile[2], per_tile
+    TX, TY = cams[0].tiles
+    per_tile = [r["n_keys"] / (TX * TY) for r, _ in runs[0]]
+    assert per_tile[0] < most < per_tile[2], per_tile
     for k, ((a, va), (b, vb)) in enumerate(zip(*runs)):
         assert np.array_equal(va, vb), k
         for name in ("rgb", "depth", "sigma", "alpha", "contrib", "tile_mask"):

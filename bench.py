@@ -132,9 +132,10 @@ def parse():
                          "city workload (the paper's large-scene setting), 1 otherwise")
     ap.add_argument("--sort-path", default="auto", choices=["auto", "depth_first", "per_tile"],
                     help="how per-tile depth order is produced (tgs_scene_set_sort_path)")
-    ap.add_argument("--blend-split", type=int, default=12,
+    ap.add_argument("--blend-split", type=int, default=None,
                     help="tiles with at least 2**N list entries are blended as four quadrant "
-                         "blocks (tgs_scene_set_blend_split; -1: never)")
+                         "blocks (tgs_scene_set_blend_split; -1: never); default: the library's, "
+                         "a threshold that follows each frame's keys")
     ap.add_argument("--copy-calibration-mb", type=int, default=0,
                     help="run one device copy of this size (for HBM counter calibration)")
     ap.add_argument("--aggregate-counters", nargs=2, metavar=("CSV", "JSON"),
@@ -432,7 +433,8 @@ def main():
     mem0 = used()
     scene_h = tgs.tgs_scene_upload(wl.scene)
     tgs.tgs_scene_set_sort_path(scene_h, SORT_MODES[args.sort_path])
-    tgs.tgs_scene_set_blend_split(scene_h, args.blend_split)
+    if args.blend_split is not None:
+        tgs.tgs_scene_set_blend_split(scene_h, args.blend_split)
     torch.cuda.synchronize()
     mem_scene = used() - mem0
     tgs.tgs_render_full(scene_h, cams[0], **out_f)
@@ -702,7 +704,7 @@ def main():
     # settings, with the kernel sources of the hash it records
     traffic_all = None
     profiled = (args.workload == "room" and args.tgb_downscale == 1 and args.sort_path == "auto"
-                and args.blend_split == 12 and args.frames is None)
+                and args.blend_split is None and args.frames is None)
     if profiled and os.path.exists(TRAFFIC_FILE):
         tr = json.load(open(TRAFFIC_FILE))
         if tr.get("kernel_source_sha") == kernel_source_hash():
@@ -838,7 +840,7 @@ def main():
         "speedup_temporal_vs_full": round(fps_t / fps_f, 3),
         "tile_rule": "3DGS 3-sigma square",
         "sort_path": args.sort_path,
-        "blend_split_log2": args.blend_split,
+        "blend_split_log2": "per frame" if args.blend_split is None else args.blend_split,
         **variants,
         "psnr_temporal_vs_full": psnr,
         "ssim_temporal_vs_full": ssim,

@@ -35,8 +35,9 @@ EXPORTED = ["tgs_params_default", "tgs_scene_upload", "tgs_scene_free", "tgs_sce
 
 # tgs_scene_set_sort_path modes
 SORT_AUTO, SORT_DEPTH_FIRST, SORT_PER_TILE = 0, 1, 2
-# tgs_scene_set_blend_split: default log2 of the list length from which tiles are
-# split into quadrant blocks, and the most tiles split per frame
+# tgs_scene_set_blend_split: the largest log2 of the list length from which tiles
+# are split into quadrant blocks where it was never called (the threshold then
+# follows each frame's keys), and the most tiles split per frame
 BLEND_SPLIT_DEFAULT, BLEND_SPLIT_MAX = 12, 1024
 
 PROF_STAGES = ["preprocess", "scan", "readback", "duplicate", "sort", "ranges", "blend_full",
@@ -325,7 +326,8 @@ def tgs_scene_set_blend_split(h, log2_min=BLEND_SPLIT_DEFAULT, max_tiles=BLEND_S
     """For later renders through the scene, tiles with at least 2**log2_min
     list entries are blended as four quadrant blocks (-1: never); if more
     than max_tiles tiles qualify, the threshold doubles until at most
-    max_tiles do."""
+    max_tiles do.  Until it is called, a scene's threshold follows each
+    frame's keys."""
     _check(lib().tgs_scene_set_blend_split(h, int(log2_min), int(max_tiles)))
 
 

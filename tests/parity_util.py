@@ -346,14 +346,16 @@ def sample_tiles_for(counts, TX, TY, seed=0, heavy=12, rand=40):
                                      np.arange((TY - 1) * TX, TY * TX, 13)])).astype(np.int64)
 
 
-# Per-scene settings of the library under test.
-DEFAULT_SPLIT = (tgs.BLEND_SPLIT_DEFAULT, tgs.BLEND_SPLIT_MAX)
+# Per-scene settings of the library under test: a fixed split threshold, so
+# that small scenes keep whole tiles (None: the scene's own, which follows each
+# frame's keys).
+FIXED_SPLIT = (tgs.BLEND_SPLIT_DEFAULT, tgs.BLEND_SPLIT_MAX)
 
 
 class Uploaded:
     """A scene on the device with its tile rule, sort path and blend split."""
 
-    def __init__(self, scene, bound=tgs.TGS_TILES_3SIGMA, sort=tgs.SORT_AUTO, split=DEFAULT_SPLIT):
+    def __init__(self, scene, bound=tgs.TGS_TILES_3SIGMA, sort=tgs.SORT_AUTO, split=FIXED_SPLIT):
         self.scene, self.bound, self.sort, self.split = scene, bound, sort, split
 
     def __enter__(self):
@@ -369,7 +371,7 @@ class Uploaded:
 
 
 def full_parity(scene, cams, sample_tiles=None, label="", bound=tgs.TGS_TILES_3SIGMA,
-                sort=tgs.SORT_AUTO, split=DEFAULT_SPLIT, by_range=False,
+                sort=tgs.SORT_AUTO, split=FIXED_SPLIT, by_range=False,
                 margin_px_frac=MARGIN_PX_FRAC):
     """tgs_render_full against the oracle: records, lists (every tile; or, with
     ``by_range``, range lengths of every tile and the lists of the sampled
@@ -413,7 +415,7 @@ def full_parity(scene, cams, sample_tiles=None, label="", bound=tgs.TGS_TILES_3S
 
 
 def temporal_parity(scene, cams, W, H, label, bound=tgs.TGS_TILES_3SIGMA, sort=tgs.SORT_AUTO,
-                    split=DEFAULT_SPLIT, sample_tiles=None, by_range=False,
+                    split=FIXED_SPLIT, sample_tiles=None, by_range=False,
                     margin_px_frac=MARGIN_PX_FRAC, **pkw):
     """tgs_render_temporal over a camera stream against the oracle's own
     schedule.  Before every frame after the first, the GPU's exported state

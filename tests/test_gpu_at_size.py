@@ -1,8 +1,8 @@
 """GPU parity at the full sizes of the object, city and stress workloads,
-in the launch configuration the benchmark times (per-frame sort path,
-default blend split with quadrant blocks for lists of 4096 entries and more;
-the city's geometry buffer downscaled by 2, the paper's large-scene setting
-of Sec. IV-B).
+in the launch configuration the benchmark times (per-frame sort path; a
+scene's own blend split, whose threshold follows each frame's keys up to lists
+of 4096 entries; the city's geometry buffer downscaled by 2, the paper's
+large-scene setting of Sec. IV-B).
 
 Object (300k Gaussians, 1280x720): every list and every pixel.  City (6M,
 1920x1080, 10M keys): every list, colour and moments on sampled tiles (the
@@ -36,8 +36,8 @@ def _device():
 def test_object_full_size():
     w = synth.workload("object", n_frames=3)
     W, H = w.cameras[0].width, w.cameras[0].height
-    full_parity(w.scene, w.cameras[:1], label="object 300k")
-    st = temporal_parity(w.scene, w.cameras, W, H, "object 300k")
+    full_parity(w.scene, w.cameras[:1], label="object 300k", split=None)
+    st = temporal_parity(w.scene, w.cameras, W, H, "object 300k", split=None)
     assert st["kinds"][0] == O.TRUE_REF and st["tgs"] >= 1
 
 
@@ -54,9 +54,9 @@ def test_city_full_size():
     log(f"[city] keys {int(counts[-1])}, {long_tiles} tiles with lists of 4096 or more "
         f"(quadrant blocks), {sample.size} sampled tiles")
     assert long_tiles > 0 and np.diff(counts)[sample].max() >= 4096
-    full_parity(w.scene, [cam], sample_tiles=sample, label="city 6M")
+    full_parity(w.scene, [cam], sample_tiles=sample, label="city 6M", split=None)
     st = temporal_parity(w.scene, w.cameras, W, H, "city 6M tgb/2", sample_tiles=sample,
-                         tgb_downscale=2)
+                         split=None, tgb_downscale=2)
     assert st["kinds"][0] == O.TRUE_REF and st["tgs"] >= 1
 
 
@@ -75,9 +75,9 @@ def test_stress_full_size():
     # seen from 5 units), so more of them take a decision within the
     # oracle's margin of a threshold: 1.9e-3 of them on the CPU
     full_parity(w.scene, [cam], sample_tiles=sample, label="stress 3M 4K", by_range=True,
-                margin_px_frac=3e-3)
+                split=None, margin_px_frac=3e-3)
     st = temporal_parity(w.scene, w.cameras, W, H, "stress 3M 4K", sample_tiles=sample,
-                         by_range=True, margin_px_frac=3e-3)
+                         by_range=True, split=None, margin_px_frac=3e-3)
     assert st["kinds"][0] == O.TRUE_REF and st["tgs"] >= 1
 
 
